@@ -1,0 +1,396 @@
+"""The framework's work as a list of timed cases.
+
+A training run of this framework is: count the corpus and lay out its
+vocabulary (build_vocab), build the Huffman tree (build_huffman), train
+epochs or chunks of an epoch (train_hs_epoch, train_ns_epoch), and score a
+held-out text between them (hs_loglik). Every case is one such call through
+the package's public functions, on inputs of the sizes that the repository's
+workloads name (100 K to 100 M tokens, 1,000 to 1,000,000 words, 50 to 300
+columns) and on odd sizes between them. The order is that of a program: text,
+tree, training, scoring.
+
+Inputs: Zipf-distributed word ranks with a topic per document (a topic's
+twentieth of the vocabulary takes half of the document's tokens), a few
+tokens out of the vocabulary, a last document that is not full. The models
+are ones late in training: rows of the length that trained vectors have, and
+the learning rate of the last of many epochs.
+"""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import torch
+
+import paper_1606_07822_amd as w2v
+
+DOC_LEN = 1000
+MIN_COUNT = 5
+TOPIC_MOD = 20          # a topic holds one word of each 20 neighbouring ranks
+TOPIC_SHARE = 0.51      # share of a document's tokens that its topic draws
+EVAL_SEED = 4
+EPOCHS = 100            # training cases run the last one: learning rates from 1/100 of the first one down
+
+
+def listed() -> list[dict]:
+    return [
+        # counting a small text: a handful of launches, latency is all there is
+        dict(name="vocab_100k_tokens", op="vocab", tokens=100_000, ids=1_000, zipf=1.0, topics=0, remap=True),
+        # counting a large one and mapping it to vocabulary indices: a pass over the text each
+        dict(name="vocab_100m_tokens", op="vocab", tokens=99_999_743, ids=1_000_000, zipf=1.05, topics=200, remap=True),
+        # the output layer's tree for the largest vocabulary
+        dict(name="huffman_1m", op="huffman", words=1_000_000, corpus=1_000_000_000, zipf=1.05),
+        # a first try on a small corpus with the default settings: small rows, few documents
+        dict(name="train_sg_v1k_d50", op="train", arch=0, words=1_000, dim=50, window=2, sample=0.0, policy=5,
+             tokens=100_000, corpus=100_000, zipf=1.0, topics=0),
+        # the paper's setting (100 columns, a vocabulary of tens of thousands), default settings
+        dict(name="train_sg_v30k_d100", op="train", arch=0, words=30_000, dim=100, window=5, sample=1e-3, policy=5,
+             tokens=10_000_000, corpus=10_000_000, zipf=1.0, topics=50),
+        # a chunk of an epoch at 200 columns, rows stored and word rows kept across centres
+        dict(name="train_sg_v100k_d200", op="train", arch=0, words=100_000, dim=200, window=5, sample=1e-4, policy=15,
+             tokens=20_000_000, corpus=100_000_000, zipf=1.0, topics=50),
+        # a chunk of an epoch of the headline workload, with the benchmark's settings
+        dict(name="train_sg_v1m_d300", op="train", arch=0, words=1_000_000, dim=300, window=5, sample=1e-5, policy=15,
+             tokens=40_000_000, corpus=1_000_000_000, zipf=1.05, topics=200, stash_from=10_000),
+        # CBOW: one walk of the path per centre, the gradient to every window word
+        dict(name="train_cbow_v100k_d300", op="train", arch=1, words=100_000, dim=300, window=5, sample=1e-4, policy=15,
+             tokens=20_000_000, corpus=100_000_000, zipf=1.0, topics=50),
+        # negative sampling on the headline workload's shape, five shared negatives
+        dict(name="train_ns5_v1m_d300", op="ns", words=1_000_000, dim=300, window=5, sample=1e-5, policy=1, negative=5,
+             tokens=40_000_000, corpus=1_000_000_000, zipf=1.05, topics=200),
+        # the deterministic mode: batches of centres against the model at their start
+        dict(name="train_sync_v30k_d100", op="sync", words=30_000, dim=100, window=5, sample=1e-3, batch=256,
+             tokens=100_000, corpus=10_000_000, zipf=1.0, topics=50),
+        # held-out scoring after an epoch: the skip-gram objective at the headline's shape
+        dict(name="loglik_sg_v1m_d300", op="loglik", arch=0, words=1_000_000, dim=300, window=5, sample=1e-5,
+             tokens=1_000_000, corpus=1_000_000_000, zipf=1.05, topics=200),
+        # held-out scoring of CBOW
+        dict(name="loglik_cbow_v100k_d300", op="loglik", arch=1, words=100_000, dim=300, window=5, sample=1e-4,
+             tokens=1_000_000, corpus=100_000_000, zipf=1.0, topics=50),
+    ]
+
+
+def _log_int(rng, lo: float, hi: float) -> int:
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng) -> dict:
+    op = rng.choice(["vocab", "huffman", "train", "train", "train", "train", "ns", "sync", "loglik", "loglik"])
+    zipf = rng.choice([1.0, 1.0, 1.05])
+    if op == "vocab":
+        tokens = _log_int(rng, 1e5, 1e8)
+        return dict(op=op, tokens=tokens, ids=_log_int(rng, 1e3, min(1e6, tokens / 20)), zipf=zipf,
+                    topics=rng.choice([0, 50, 200]), remap=rng.random() < 0.75)
+    words = _log_int(rng, 1e3, 1e6)
+    if op == "huffman":
+        return dict(op=op, words=words, corpus=words * rng.choice([100, 1000]), zipf=zipf)
+    dim = rng.choice([rng.randint(40, 320), rng.randint(321, 512), 50, 64, 100, 128, 200, 256, 300])
+    window = rng.choice([2, 3, 5, 5, 5, 5, 8])
+    case = dict(op=op, words=words, dim=dim, window=window, sample=rng.choice([1e-3, 1e-4, 1e-5]), zipf=zipf,
+                topics=rng.choice([0, 50, 200]))
+    # tokens: up to what costs as much as the headline's chunk (rows touched by each kept centre, times columns)
+    unit = _kept_share(case) * dim * (window + 1)
+    if op == "sync":
+        # batches that stay stable: a batch's summed changes of the tree's top may not overshoot
+        case.update(batch=rng.choice([64, 128, 256]), dim=min(dim, 320), tokens=_log_int(rng, 1e4, 1e5))
+    elif op == "loglik":
+        case.update(arch=rng.choice([0, 0, 1]), tokens=_log_int(rng, 3e4, 1e6))
+    else:
+        most = min(4e7, 4e7 * 0.3 * 300 * 6 / unit)
+        case.update(tokens=_log_int(rng, min(1e5, most / 2), most))
+        if op == "ns":
+            case.update(policy=rng.choice([1, 3]), negative=rng.choice([3, 5, 7]))
+        else:
+            arch = rng.choice([0, 0, 1])
+            case.update(arch=arch, policy=rng.choice([5, 7, 15]))
+    case["corpus"] = max(case["tokens"], 100 * words)
+    return case
+
+
+# ------------------------------------------------------------------ inputs
+def _probs(n: int, zipf: float) -> np.ndarray:
+    p = np.arange(1, n + 1, dtype=np.float64) ** -zipf
+    return p / p.sum()
+
+
+def _counts(case: dict) -> np.ndarray:
+    """Counts of the case's corpus, in descending order (the vocabulary's), none below MIN_COUNT."""
+    return (_probs(case["words"], case["zipf"]) * case["corpus"]).astype(np.int64) + MIN_COUNT
+
+
+def _gen(seed: int, role: int) -> torch.Generator:
+    return torch.Generator(device="cuda").manual_seed((seed * 1_000_003 + role) & 0x7FFFFFFF)
+
+
+def _text(n: int, ids: int, zipf: float, topics: int, seed: int, unknown: float = 0.0) -> torch.Tensor:
+    """int32[n] word ranks (-1 for a share `unknown`), in documents of DOC_LEN with a topic each."""
+    g = _gen(seed, 1)
+    edges = torch.from_numpy(np.cumsum(_probs(ids, zipf))).cuda()
+    out = torch.empty(n, dtype=torch.int32, device="cuda")
+    step = 20_000 * DOC_LEN
+    for lo in range(0, n, step):
+        m = min(step, n - lo)
+        r = torch.searchsorted(edges, torch.rand(m, generator=g, device="cuda", dtype=torch.float64))
+        r.clamp_(max=ids - 1)
+        if topics:
+            docs = -(-m // DOC_LEN)
+            topic = torch.randint(topics, (docs,), generator=g, device="cuda").repeat_interleave(DOC_LEN)[:m]
+            group = r // TOPIC_MOD
+            mine = (group * TOPIC_MOD + (group * 40_503 + topic * 9_973) % TOPIC_MOD).clamp_(max=ids - 1)
+            r = torch.where(torch.rand(m, generator=g, device="cuda") < TOPIC_SHARE, mine, r)
+        if unknown:
+            r = torch.where(torch.rand(m, generator=g, device="cuda") < unknown, -1, r)
+        out[lo:lo + m] = r.to(torch.int32)
+    return out
+
+
+def _rows(n: int, dim: int, scale: float, seed: int, role: int) -> torch.Tensor:
+    """float32[n, stride] rows as training leaves them: normal entries, zero padding."""
+    rows = torch.zeros(n, w2v.padded_stride(dim), dtype=torch.float32, device="cuda")
+    rows[:, :dim] = torch.randn(n, dim, generator=_gen(seed, role), device="cuda") * scale
+    return rows
+
+
+def _params(case: dict) -> w2v.Params:
+    common = dict(window=case["window"], sample=case["sample"], corpus_tokens=case["corpus"], doc_len=DOC_LEN,
+                  n_epochs=EPOCHS, epoch=EPOCHS - 1)
+    op = case["op"]
+    if op == "loglik":
+        return w2v.Params(window=case["window"], sample=case["sample"], arch=case["arch"], seed=EVAL_SEED)
+    if op == "sync":
+        return w2v.Params(mode=1, sync_batch=case["batch"], **common)
+    if op == "ns":
+        return w2v.Params(write_policy=case["policy"], negative=case["negative"], **common)
+    stash = case.get("stash_from")
+    return w2v.Params(arch=case["arch"], write_policy=case["policy"], span_stash=int(stash is not None),
+                      stash_from=stash or 0, alpha0=0.05 if case["arch"] == 1 else 0.025, **common)
+
+
+def prepare(case: dict, seed: int) -> dict:
+    op = case["op"]
+    state = {"op": op}
+    if op == "vocab":
+        # the most frequent 19 of 20 ids are drawn, and each of them MIN_COUNT times besides; the others stay
+        # below MIN_COUNT: as many words are kept and dropped in every text
+        ids, kept = case["ids"], case["ids"] * 19 // 20
+        text = _text(case["tokens"], kept, case["zipf"], case["topics"], seed)
+        extra = torch.cat([torch.arange(kept, device="cuda").repeat(MIN_COUNT), torch.arange(kept, ids, device="cuda")])
+        step = case["tokens"] // extra.numel()
+        text[:extra.numel() * step:step] = extra[torch.randperm(extra.numel(), generator=_gen(seed, 5), device="cuda")].int()
+        state.update(tokens=text, ids=ids, remap=case["remap"])
+        return state
+    counts = _counts(case)
+    if op == "huffman":
+        # counts of a corpus drawn from the distribution: Poisson around their expectations
+        c = torch.from_numpy(counts).cuda().double()
+        c = (c + torch.sqrt(c) * torch.randn(c.numel(), generator=_gen(seed, 2), device="cuda", dtype=torch.float64))
+        state["counts"] = c.round().clamp_(min=MIN_COUNT).long().sort(descending=True).values
+        state["points"] = torch.full((32 * case["words"],), -1, dtype=torch.int32, device="cuda")
+        return state
+    vc = torch.from_numpy(counts).cuda()
+    words, dim = case["words"], case["dim"]
+    state["tokens"] = _text(case["tokens"], words, case["zipf"], case["topics"], seed, unknown=0.01)
+    syn0 = _rows(words, dim, 0.15, seed, 3)
+    if op == "ns":
+        syn1 = _rows(words, dim, 0.1, seed, 4)
+        state["noise"] = w2v.build_noise_table(vc)
+        tree = None
+    else:
+        syn1 = _rows(words - 1, dim, 0.1, seed, 4)
+        tree = w2v.build_huffman(vc)
+    state["model"] = w2v.Model(syn0, syn1, dim, vc, int(counts.sum()), tree)
+    state["params"] = _params(case)
+    if op in ("train", "sync"):
+        n = w2v.train_workspace_bytes(state["model"], case["tokens"], state["params"])
+        state["workspace"] = torch.empty(n, dtype=torch.uint8, device="cuda")
+    return state
+
+
+def run(state: dict):
+    op = state["op"]
+    if op == "vocab":
+        v = w2v.build_vocab(state["tokens"], state["ids"], MIN_COUNT, remap=state["remap"])
+        out = {"counts_by_id": v.counts_by_id, "vocab_ids": v.vocab_ids, "vocab_counts": v.vocab_counts,
+               "id_to_vocab": v.id_to_vocab, "words": v.V, "train_words": v.train_words}
+        if v.tokens is not None:
+            out["tokens"] = v.tokens
+        return out
+    if op == "huffman":
+        t = w2v.build_huffman(state["counts"])
+        state["points"][:t.points.numel()] = t.points   # into a buffer of the program's, as long for every corpus
+        return {"codelen": t.codelen, "code": t.code, "point_off": t.point_off, "points": state["points"],
+                "max_len": t.max_len}
+    if op == "loglik":
+        total, terms, nodes = w2v.hs_loglik(state["model"], state["tokens"], state["params"])
+        return {"total": np.float64(total), "terms": terms, "nodes": nodes}
+    if op == "ns":
+        stats = w2v.train_ns_epoch(state["model"], state["noise"], state["tokens"], state["params"])
+    else:
+        stats = w2v.train_hs_epoch(state["model"], state["tokens"], state["params"], workspace=state["workspace"])
+    syn0, syn1 = state["model"].vectors()
+    return {"syn0": syn0, "syn1": syn1, "stats": stats}
+
+
+# ------------------------------------------------------------------ work and tolerances
+def _keep(case: dict) -> tuple[np.ndarray, np.ndarray]:
+    """Each word's probability, and the probability that subsampling keeps one of its tokens."""
+    p = _probs(case["words"], case["zipf"])
+    if case["sample"] <= 0:
+        return p, np.ones_like(p)
+    q = case["sample"] / p
+    return p, np.minimum(1.0, np.sqrt(q) + q)
+
+
+def _kept_share(case: dict) -> float:
+    p, keep = _keep(case)
+    return float((p * keep).sum())
+
+
+def work(case: dict) -> dict:
+    op = case["op"]
+    if op == "vocab":
+        # the text read once; counts, order and map written; the mapped text written
+        return {"bytes": case["tokens"] * (8 if case["remap"] else 4) + case["ids"] * 24, "flops": 0}
+    if op == "huffman":
+        # counts read; code lengths, codes, offsets and points written (about the entropy's points per word)
+        mean_len = float(np.log2(1.0 / _probs(case["words"], case["zipf"])).mean())
+        return {"bytes": case["words"] * (8 + 1 + 8 + 4 + 4 * mean_len), "flops": 0}
+    p, keep = _keep(case)
+    kept = case["tokens"] * float((p * keep).sum())
+    depth = float((p * keep * np.ceil(np.log2(1.0 / p))).sum() / (p * keep).sum())
+    pairs = kept * (case["window"] + 1)
+    rows = 2 * case["words"] * case["dim"] * 4
+    if op == "loglik":
+        touched = min(1.0, kept * (1 + depth / 4) / case["words"])
+        dots = (kept if case["arch"] == 1 else pairs) * depth
+        return {"bytes": case["tokens"] * 4 + rows * touched, "flops": 2 * case["dim"] * dots}
+    # each word row and node or output row read and written once, the text read once; a dot product and
+    # two updates (6 flops a column) for each update of a row by a pair or, in CBOW, by a centre
+    inputs = kept if case.get("arch") == 1 else pairs
+    targets = case["negative"] + 1 if op == "ns" else depth
+    return {"bytes": case["tokens"] * 4 + 2 * rows, "flops": 6 * case["dim"] * inputs * targets}
+
+
+def tolerance(case: dict):
+    op = case["op"]
+    if op in ("vocab", "huffman"):
+        return "exact"
+    if op == "loglik":
+        # 32-bit dot products, 64-bit sums of millions of terms: within 6e-11 of exact()
+        return {"rel": 1e-9}
+    if op == "sync":
+        # 32-bit rows and gradients, exact sums: within 9e-8 of exact()
+        return {"rel": 5e-7}
+    # lock-free: two passes over the same inputs differ where wavefronts meet on the rows of frequent words and
+    # of the tree's top; by 0.3 to 1.5 % of the rows' norm, and by up to 0.4 of it at single values, at twice
+    # this learning rate
+    return {"rel": 0.03, "max": 0.99}
+
+
+# ------------------------------------------------------------------ the same in 64 bits
+_M32 = 0xFFFFFFFF
+
+
+def _philox(c0, c1, epoch: int, seed: int):
+    """First two words of Philox4x32-10 (Salmon et al., SC'11) with counter (c0, c1, epoch, 0)."""
+    c0, c1 = c0.clone(), c1.clone()
+    c2, c3 = torch.full_like(c0, epoch), torch.zeros_like(c0)
+    k0, k1 = seed & _M32, seed >> 32
+    for _ in range(10):
+        a, b = c0 * 0xD2511F53, c2 * 0xCD9E8D57
+        c0, c1, c2, c3 = (((b >> 32) & _M32) ^ c1 ^ k0, b & _M32, ((a >> 32) & _M32) ^ c3 ^ k1, a & _M32)
+        k0, k1 = (k0 + 0x9E3779B9) & _M32, (k1 + 0xBB67AE85) & _M32
+    return c0, c1
+
+
+def _centres(state: dict):
+    """Kept tokens in stream order: word, document, raw position, and each side's window words as indices."""
+    p, m, tok = state["params"], state["model"], state["tokens"].long()
+    raw = torch.arange(tok.numel(), device=tok.device)
+    r0, r1 = _philox(raw & _M32, raw >> 32, p.epoch, p.seed)
+    if p.sample > 0:
+        q = (p.sample * float(m.train_words)) / m.vocab_counts.double()
+        keep = torch.sqrt(q) + q
+        thr = torch.where(keep >= 1.0, torch.tensor(2.0 ** 32, device=tok.device, dtype=torch.float64),
+                          torch.floor(keep * 2.0 ** 32)).long()
+    else:
+        thr = torch.full((m.V,), 1 << 32, device=tok.device)
+    at = torch.nonzero((tok >= 0) & (r0 < thr[tok.clamp(min=0)])).view(-1)
+    eff = p.window - ((r1[at] * p.window) >> 32)
+    return tok[at], at // p.doc_len, at, eff
+
+
+def _windows(word, doc, eff, lo: int, hi: int, window: int):
+    """Window words of the kept centres lo..hi: indices [n, 2 window] and which of them there are."""
+    off = torch.tensor([o for o in range(-window, window + 1) if o], device=word.device)
+    i = torch.arange(lo, hi, device=word.device)[:, None]
+    c = i + off
+    ok = (c >= 0) & (c < word.numel()) & (off.abs() <= eff[lo:hi, None])
+    c = c.clamp(0, word.numel() - 1)
+    return c, ok & (doc[c] == doc[lo:hi, None])
+
+
+def _paths(model, word):
+    """Path nodes [n, longest], which of them there are, and their code bits."""
+    t = model.tree
+    length = t.codelen[word].long()
+    j = torch.arange(int(length.max()), device=word.device)
+    ok = j < length[:, None]
+    at = (t.point_off[word].long()[:, None] + j).clamp(max=t.points.numel() - 1)
+    return t.points[at].long(), ok, ((t.code[word][:, None] >> j) & 1).double()
+
+
+def _exact_loglik(state: dict, cbow: bool):
+    model, p = state["model"], state["params"]
+    syn0, syn1 = model.vectors()
+    word, doc, _, eff = _centres(state)
+    total, terms, nodes = 0.0, 0, 0
+    step = 2048
+    for lo in range(0, word.numel(), step):
+        hi = min(word.numel(), lo + step)
+        c, ok = _windows(word, doc, eff, lo, hi, p.window)
+        pt, live, bit = _paths(model, word[lo:hi])
+        x = syn0[word[c]].double() * ok[:, :, None]
+        if cbow:
+            n = ok.sum(1)
+            x = (x.sum(1) / n.clamp(min=1)[:, None])[:, None, :]
+            ok = (n > 0)[:, None]
+        z = torch.bmm(x, syn1[pt].double().transpose(1, 2).contiguous()) * (1 - 2 * bit)[:, None, :]
+        use = ok[:, :, None] & live[:, None, :]
+        total += float(torch.where(use, torch.nn.functional.logsigmoid(z), torch.zeros_like(z)).sum())
+        terms += int(ok.sum())
+        nodes += int(use.sum())
+    return {"total": np.float64(total), "terms": terms, "nodes": nodes}
+
+
+def _exact_sync(state: dict):
+    model, p = state["model"], state["params"]
+    syn0, syn1 = (t.double() for t in model.vectors())
+    word, doc, raw, eff = _centres(state)
+    block = (p.epoch * p.corpus_tokens + raw) // 10_000
+    alpha = p.alpha0 * torch.clamp(1.0 - (block * 10_000).double() / (p.n_epochs * p.corpus_tokens + 1), min=1e-4)
+    for b in range(0, word.numel(), p.sync_batch):
+        d0, d1 = torch.zeros_like(syn0), torch.zeros_like(syn1)
+        end = min(word.numel(), b + p.sync_batch)
+        for lo in range(b, end, 2048):
+            hi = min(end, lo + 2048)
+            c, ok = _windows(word, doc, eff, lo, hi, p.window)
+            pt, live, bit = _paths(model, word[lo:hi])
+            x, y = syn0[word[c]], syn1[pt]
+            z = torch.bmm(x, y.transpose(1, 2).contiguous())
+            g = alpha[lo:hi, None, None] * (1 - bit[:, None, :] - torch.sigmoid(z))
+            g = torch.where(ok[:, :, None] & live[:, None, :], g, torch.zeros_like(g))
+            d0.index_add_(0, word[c].view(-1), torch.bmm(g, y).view(-1, model.dim))
+            d1.index_add_(0, pt.view(-1), torch.bmm(g.transpose(1, 2).contiguous(), x).view(-1, model.dim))
+        syn0 += d0
+        syn1 += d1
+    return {"syn0": syn0, "syn1": syn1, "stats": None}
+
+
+def exact(case: dict, seed: int):
+    # vocabulary and tree are whole numbers; the lock-free modes have no one result
+    if case["op"] == "loglik":
+        return _exact_loglik(prepare(case, seed), case["arch"] == 1)
+    if case["op"] == "sync":
+        return _exact_sync(prepare(case, seed))
+    return None
