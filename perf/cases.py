@@ -282,8 +282,7 @@ def tolerance(case: dict):
         # 32-bit rows and gradients, exact sums: within 9e-8 of exact()
         return {"rel": 5e-7}
     # lock-free: two passes over the same inputs differ where wavefronts meet on the rows of frequent words and
-    # of the tree's top; by 0.3 to 1.5 % of the rows' norm, and by up to 0.4 of it at single values, at twice
-    # this learning rate
+    # of the tree's top: measured up to 0.73 % of the rows' norm, and up to a quarter of it at single values
     return {"rel": 0.03, "max": 0.99}
 
 
