@@ -21,8 +21,7 @@ int run_sample_pairs(const int32_t *, int64_t, int32_t, const int64_t *, int64_t
                      int64_t *, int64_t, uint8_t *, int64_t *, int64_t *, uint64_t *, void *, hipStream_t);
 size_t train_lds_bytes(int32_t cache_k, int32_t dim, bool delta);
 int train_launch_shape(int arch, int dim, int cache_k, bool delta, bool buf, int workers, int64_t n_units, int *grid,
-                       int *waves,
-                       bool slide = false, bool stash = false);
+                       int *waves);
 int64_t train_egrad_floats(int arch, int dim, bool buf, int stride, int window, int waves);
 int train_word_span(int arch, int dim, bool buf, int write_policy, int window);
 int launch_train_async(TrainArgs a, int arch, int window, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s,

@@ -6,6 +6,8 @@ import pytest
 import torch
 
 import oracle
+import synth
+from gpu_common import log, oracle_side, row_rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -56,3 +58,39 @@ def test_huffman_too_deep_at_any_generation_is_an_error(w2v, V):
     with pytest.raises(w2v.W2VError) as e:
         w2v.build_huffman(to_dev(np.array(fib[::-1], np.int64)))
     assert e.value.code == w2v.W2V_E_RANGE
+
+
+# ------------------------------------------------------------- word-row changes kept across centres
+# Skip-gram rows of up to 128 floats with windows of up to 5 keep a word row's change in the wavefront until its
+# position leaves the window: the widest and narrowest row of each variant, windows of both, every write policy
+# that takes it, no subsampling over 1,000 words (repeated words in most windows), short documents, and the
+# settings that fall back (a cache too large for the centre records, windows above 5). The bar is the one of the
+# other single-worker tests: sums in another order and the fast sigmoid, carried through the updates.
+@pytest.mark.parametrize("name,sample,dim,win,wp,k,doc_len", [
+    ("tiny_sg_v1k_d50", 0.0, 50, 2, 5, 31, 1000), ("tiny_sg_v1k_d50", 0.0, 64, 5, 7, 31, 1000),
+    ("tiny_sg_v1k_d50", 0.0, 65, 5, 5, 31, 1000), ("tiny_sg_v1k_d50", 0.0, 1, 3, 15, 7, 1000),
+    ("tiny_sg_v1k_d50", 0.0, 128, 2, 7, 0, 1000), ("tiny_sg_v1k_d50", 0.0, 100, 4, 1, 0, 7),
+    ("tiny_sg_v1k_d50", 0.0, 33, 1, 5, 31, 3), ("tiny_sg_v1k_d50", 0.0, 100, 5, 5, 31, 129),
+    ("sg_v30k_d100", 1e-3, 100, 5, 5, 31, 1000), ("sg_v30k_d100", 1e-3, 127, 3, 7, 31, 1000),
+    ("sg_v30k_d100", 1e-3, 100, 5, 5, 120, 1000), ("sg_v30k_d100", 1e-3, 100, 6, 5, 31, 1000),
+    ("sg_v30k_d100", 1e-3, 64, 10, 7, 31, 1000),
+])
+def test_narrow_rows_single_worker_matches_oracle(w2v, name, sample, dim, win, wp, k, doc_len):
+    log(f"narrow rows {name} dim={dim} window={win} write_policy={wp} k={k} doc_len={doc_len}")
+    s = oracle_side(name)
+    voc = w2v.build_vocab(to_dev(s.tok), s.w.vocab, s.w.min_count)
+    tree = w2v.build_huffman(voc.vocab_counts)
+    tv = s.tv[:3001]
+    syn0, syn1 = synth.init_weights(s.voc.V, dim, syn1_scale=0.5 / dim)
+    a0, a1 = syn0.copy(), syn1.copy()
+    op = oracle.params(s.voc.V, dim, window=win, sample=sample, train_words=s.voc.train_words,
+                       corpus_tokens=s.tv.size, cache_k=k, flush_every=10, order=1, doc_len=doc_len)
+    ost = oracle.train(a0, a1, s.tree, tv, op)
+    model = w2v.make_model(syn0, syn1, voc, tree, stride=(dim + 3) // 4 * 4, pad_value=float("nan"))
+    p = w2v.Params(window=win, sample=sample, corpus_tokens=s.tv.size, cache_k=k, flush_every=10, workers=1,
+                   write_policy=wp, doc_len=doc_len)
+    st = w2v.train_hs_epoch(model, to_dev(tv), p).cpu().numpy()
+    assert list(st) == list(ost)
+    g0, g1 = (t.cpu().numpy() for t in model.vectors())
+    assert row_rel_err(g0, a0) <= 1e-4
+    assert row_rel_err(g1[:s.voc.V - 1], a1) <= 1e-4
