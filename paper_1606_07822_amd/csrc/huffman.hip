@@ -11,6 +11,7 @@
 #include <algorithm>
 
 #include "w2v_internal.h"
+#include "w2v_scan.h"
 
 namespace w2v {
 namespace {
@@ -50,22 +51,6 @@ __global__ void k_check_descending(const int64_t *__restrict__ counts, int32_t V
 // Leaves in ascending count: position p is vocabulary index V-1-p.
 __device__ __forceinline__ int64_t leaf_val(const int64_t *__restrict__ counts, int32_t V, int32_t p) {
     return counts[V - 1 - p];
-}
-
-// First index in [lo, hi) at which pred (true up to some index, false from there on) is false, by one
-// wavefront: 64 probes a step.
-template <class F>
-__device__ __forceinline__ int32_t wave_partition_point(int32_t lo, int32_t hi, F pred) {
-    const int lane = lane_id();
-    while (lo < hi) {
-        const int32_t step = (hi - lo + kWave - 1) / kWave;
-        const int64_t at = lo + static_cast<int64_t>(lane + 1) * step - 1;
-        const int n = __popcll(__ballot(at < hi && pred(static_cast<int32_t>(at))));
-        const int64_t end = lo + static_cast<int64_t>(n + 1) * step - 1;   // the first failing probe, if there is one
-        lo += n * step;
-        hi = end < hi ? static_cast<int32_t>(end) : hi;
-    }
-    return lo;
 }
 
 // Every workgroup's writes before the barrier are visible to every workgroup after it. The launch is

@@ -45,7 +45,7 @@ struct SyncArgs {
     unsigned long long *d1;    // [V-1][dim] of syn1
     int32_t *flag0, *flag1;    // touched rows
     int32_t *list0, *list1;
-    int32_t *cnt;              // [2] list lengths
+    int32_t *cnt;              // [2] list lengths of this batch
     unsigned long long *stats; // kept, pairs, nodes
 };
 
@@ -59,18 +59,23 @@ __device__ __forceinline__ void touch(int32_t *flag, int32_t *list, int32_t *cnt
     if (atomicExch(&flag[r], 1) == 0) list[atomicAdd(cnt, 1)] = r;
 }
 
-template <int NE>
-__global__ __launch_bounds__(256) void k_sync_grad(SyncArgs a) {
-    const int lane = lane_id();
-    const int64_t gi = a.c_lo + (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) / kWave;
-    if (gi >= a.c_hi) return;
+// One workgroup per centre, its eight wavefronts sharing the path: wavefront w takes the nodes w, w+8, ... and
+// walks them once for a group of GW window words, whose dot products are reduced four at a time. The fixed-point
+// sums are exact in any order, so a node's change is summed over the group's words in registers, and a word's
+// over all nodes in registers and LDS, before one atomic add each. What bounds a batch is the 64-bit adds to the
+// rows its centres share and then the chain of a centre's loads, products and adds: one wavefront per centre
+// with an add per pair, node and column on either side took 206 us for 256 centres (V = 30K, d = 100, window 5);
+// this takes about 17 (an epoch of 305 such batches 7.6 instead of 64.8 ms; with four wavefronts 8.4, and with
+// the words' sums added by each of four or eight wavefronts 10.4 and 15.0).
+constexpr int kSyncWaves = 8;
+template <int NE, int GW>
+__global__ __launch_bounds__(kSyncWaves *kWave) void k_sync_grad(SyncArgs a) {
+    __shared__ unsigned long long s_dx[GW][NE * kWave];   // the group's words' changes over all nodes
+    const int lane = lane_id(), wid = static_cast<int>(threadIdx.x / kWave);
+    const int64_t gi = a.c_lo + blockIdx.x;
     // document of kept centre gi: last d with kept_off[d] <= gi
-    int64_t lo = 0, hi = a.n_docs - 1;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi + 1) >> 1;
-        if (a.kept_off[mid] <= gi) lo = mid; else hi = mid - 1;
-    }
-    const int64_t d = lo;
+    const int64_t d = wave_partition_point(0, static_cast<int32_t>(a.n_docs),
+                                           [&](int32_t m) { return a.kept_off[m] <= gi; }) - 1;
     const int j = static_cast<int>(gi - a.kept_off[d]);
     const int nk = a.doc_kept[d];
     const int64_t base = d * a.doc_len;
@@ -80,7 +85,7 @@ __global__ __launch_bounds__(256) void k_sync_grad(SyncArgs a) {
     const int clo = max(0, j - eff), chi = min(nk - 1, j + eff);
     const int P = chi - clo;
     const int len = a.codelen[v];
-    if (lane == 0) {
+    if (threadIdx.x == 0) {
         atomicAdd(&a.stats[0], 1ull);
         atomicAdd(&a.stats[1], static_cast<unsigned long long>(P));
         atomicAdd(&a.stats[2], static_cast<unsigned long long>(P) * len);
@@ -90,66 +95,113 @@ __global__ __launch_bounds__(256) void k_sync_grad(SyncArgs a) {
     const float alpha = a.alpha_tab[g / 10000 - a.blk0];
     const uint64_t code = a.code[v];
     const int my_pt = (lane < len) ? a.points[a.point_off[v] + lane] : 0;
-    for (int p = 0; p < P; ++p) {
-        const int c = clo + p + ((clo + p >= j) ? 1 : 0);
-        const int w = a.kept_vid[base + c];
-        float x[NE];
+    const int cq = clo + lane + ((clo + lane >= j) ? 1 : 0);
+    const int my_w = (lane < P) ? a.kept_vid[base + cq] : 0;   // lane q: the q-th window word
+    if (wid == 0 && lane < P) touch(a.flag0, a.list0, a.cnt, my_w);
+    if (wid == 1 && lane < len) touch(a.flag1, a.list1, a.cnt + 1, my_pt);
+    for (int p0 = 0; p0 < P; p0 += GW) {
+        const int n_words = min(GW, P - p0);
+        if (p0 > 0) __syncthreads();   // the group before is written out
+        for (int i = threadIdx.x; i < n_words * NE * kWave; i += blockDim.x) (&s_dx[0][0])[i] = 0;
+        __syncthreads();
+        float x[GW][NE];
+        long long dx[GW][NE];
 #pragma unroll
-        for (int i = 0; i < NE; ++i) {
-            const int col = lane + i * kWave;
-            x[i] = col < a.dim ? a.syn0[static_cast<int64_t>(w) * a.stride + col] : 0.0f;
+        for (int p = 0; p < GW; ++p) {
+            const int w = __builtin_amdgcn_readlane(my_w, min(p0 + p, kWave - 1));
+            const bool in = p0 + p < P;
+            buf_load_row<NE>(x[p], row_rsrc(const_cast<float *>(a.syn0), in ? w : 0, a.stride, in ? a.dim * 4 : 0), lane);
+#pragma unroll
+            for (int i = 0; i < NE; ++i) dx[p][i] = 0;
         }
-        for (int jn = 0; jn < len; ++jn) {
-            const int n = __builtin_amdgcn_readlane(my_pt, jn);
+        auto load_node = [&](float(&y)[NE], int jn) {   // zeros past the path's end
+            const int n = __builtin_amdgcn_readlane(my_pt, min(jn, kWave - 1));
+            buf_load_row<NE>(y, row_rsrc(const_cast<float *>(a.syn1), jn < len ? n : 0, a.stride,
+                                         jn < len ? a.dim * 4 : 0), lane);
+        };
+        float next[NE];
+        load_node(next, wid);
+        for (int jn = wid; jn < len; jn += kSyncWaves) {
+            const int n = __builtin_amdgcn_readlane(my_pt, min(jn, kWave - 1));
             const float t = static_cast<float>((code >> jn) & 1ull);
             float y[NE];
-            float s = 0.0f;
+            long long dy[NE];
 #pragma unroll
-            for (int i = 0; i < NE; ++i) {
-                const int col = lane + i * kWave;
-                y[i] = col < a.dim ? a.syn1[static_cast<int64_t>(n) * a.stride + col] : 0.0f;
-                s = fmaf(x[i], y[i], s);
-            }
-            const float z = wave_sum(s);
-            const float f = 1.0f / (1.0f + expf(-z));
-            const float gr = (1.0f - t - f) * alpha;
-            if (lane == 0) touch(a.flag1, a.list1, a.cnt + 1, n);
+            for (int i = 0; i < NE; ++i) y[i] = next[i];
+            load_node(next, jn + kSyncWaves);
 #pragma unroll
-            for (int i = 0; i < NE; ++i) {
-                const int col = lane + i * kWave;
-                if (col < a.dim) {
-                    atomicAdd(&a.d1[static_cast<int64_t>(n) * a.dim + col],
-                              to_fixed(static_cast<double>(gr) * static_cast<double>(x[i])));
-                    atomicAdd(&a.d0[static_cast<int64_t>(w) * a.dim + col],
-                              to_fixed(static_cast<double>(gr) * static_cast<double>(y[i])));
+            for (int i = 0; i < NE; ++i) dy[i] = 0;
+#pragma unroll
+            for (int c = 0; c < GW; c += 4) {
+                if (p0 + c < P) {
+                    const float z = reduce4(dot_partial<NE>(x[c], y), dot_partial<NE>(x[c + 1], y),
+                                            dot_partial<NE>(x[c + 2], y), dot_partial<NE>(x[c + 3], y));
+                    const float f = 1.0f / (1.0f + expf(-z));
+                    const float gr = (1.0f - t - f) * alpha;   // lanes 16 r ..: window word p0 + c + r
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (p0 + c + r < P) {
+                            const double gp = static_cast<double>(__builtin_bit_cast(
+                                float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, gr), 16 * r)));
+#pragma unroll
+                            for (int i = 0; i < NE; ++i) {
+                                dy[i] += static_cast<long long>(to_fixed(gp * static_cast<double>(x[c + r][i])));
+                                dx[c + r][i] += static_cast<long long>(to_fixed(gp * static_cast<double>(y[i])));
+                            }
+                        }
+                    }
                 }
             }
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+                const int col = lane + i * kWave;
+                if (col < a.dim)
+                    atomicAdd(&a.d1[static_cast<int64_t>(n) * a.dim + col], static_cast<unsigned long long>(dy[i]));
+            }
         }
-        if (lane == 0) touch(a.flag0, a.list0, a.cnt, w);
+        if (wid < len) {
+#pragma unroll
+            for (int p = 0; p < GW; ++p)
+                if (p < n_words)
+#pragma unroll
+                    for (int i = 0; i < NE; ++i)
+                        atomicAdd(&s_dx[p][lane + i * kWave], static_cast<unsigned long long>(dx[p][i]));
+        }
+        __syncthreads();
+        for (int p = wid; p < n_words; p += kSyncWaves) {
+            const int w = __builtin_amdgcn_readlane(my_w, p0 + p);
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+                const int col = lane + i * kWave;
+                if (col < a.dim) atomicAdd(&a.d0[static_cast<int64_t>(w) * a.dim + col], s_dx[p][col]);
+            }
+        }
     }
 }
 
-// one wave per touched row: row += (float)(delta 2^-40); clear delta and flag
-__global__ __launch_bounds__(256) void k_sync_apply(float *w, int32_t stride, int32_t dim, unsigned long long *dl,
-                                                    int32_t *flag, const int32_t *list, const int32_t *cnt) {
+// one wave per touched row of either matrix: row += (float)(delta 2^-40); clear delta and flag, and the other
+// batch parity's list lengths, which the next batch fills
+__global__ __launch_bounds__(256) void k_sync_apply(SyncArgs a, float *syn0, float *syn1, int32_t *next_cnt) {
     const int lane = lane_id();
-    const int n = *cnt;
+    const int n0 = a.cnt[0], n = n0 + a.cnt[1];
+    if (blockIdx.x == 0 && threadIdx.x < 2) next_cnt[threadIdx.x] = 0;
     const int nw = gridDim.x * blockDim.x / kWave;
     for (int k = (blockIdx.x * blockDim.x + threadIdx.x) / kWave; k < n; k += nw) {
-        const int r = list[k];
-        for (int col = lane; col < dim; col += kWave) {
-            unsigned long long *q = &dl[static_cast<int64_t>(r) * dim + col];
-            const double dv = ldexp(static_cast<double>(static_cast<long long>(*q)), -kFrac);
-            float *x = &w[static_cast<int64_t>(r) * stride + col];
-            *x = *x + static_cast<float>(dv);
-            *q = 0ull;
+        const bool words = k < n0;
+        const int r = words ? a.list0[k] : a.list1[k - n0];
+        unsigned long long *dl = (words ? a.d0 : a.d1) + static_cast<int64_t>(r) * a.dim;
+        float *row = (words ? syn0 : syn1) + static_cast<int64_t>(r) * a.stride;
+        for (int col = lane; col < a.dim; col += kWave) {
+            const double dv = ldexp(static_cast<double>(static_cast<long long>(dl[col])), -kFrac);
+            row[col] = row[col] + static_cast<float>(dv);
+            dl[col] = 0ull;
         }
-        if (lane == 0) flag[r] = 0;
+        if (lane == 0) (words ? a.flag0 : a.flag1)[r] = 0;
     }
 }
 
 __global__ void k_reset_counts(int32_t *cnt) {
-    if (threadIdx.x < 2) cnt[threadIdx.x] = 0;
+    if (threadIdx.x < 4) cnt[threadIdx.x] = 0;
 }
 
 __global__ void k_zero_u64_range(unsigned long long *p, int64_t n) {
@@ -168,14 +220,16 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_kept(const int32_t *__res
 }
 
 using SyncFn = void (*)(SyncArgs);
+// window words taken together: a whole window of half-width 5 where its rows and their 64-bit sums fit the
+// registers
 SyncFn pick_sync(int dim) {
     const int ne = (dim + kWave - 1) / kWave;
-    if (ne <= 1) return k_sync_grad<1>;
-    if (ne <= 2) return k_sync_grad<2>;
-    if (ne <= 4) return k_sync_grad<4>;
-    if (ne <= 5) return k_sync_grad<5>;
-    if (ne <= 8) return k_sync_grad<8>;
-    return k_sync_grad<16>;
+    if (ne <= 1) return k_sync_grad<1, 12>;
+    if (ne <= 2) return k_sync_grad<2, 12>;
+    if (ne <= 4) return k_sync_grad<4, 8>;
+    if (ne <= 5) return k_sync_grad<5, 8>;
+    if (ne <= 8) return k_sync_grad<8, 4>;
+    return k_sync_grad<16, 4>;
 }
 
 }  // namespace
@@ -186,7 +240,7 @@ size_t sync_extra_bytes(int32_t V, int32_t dim, int64_t n_docs) {
     c.take<unsigned long long>(static_cast<size_t>(V) * dim);            // d0
     c.take<unsigned long long>(static_cast<size_t>(V) * dim);            // d1
     c.take<int32_t>(static_cast<size_t>(V) * 4);                         // flags, lists
-    c.take<int32_t>(2);
+    c.take<int32_t>(4);                                                  // list lengths of even and odd batches
     return c.used();
 }
 
@@ -221,13 +275,13 @@ int run_train_sync(const w2v_model *m, const w2v_params *p, const SampleBufs &b,
     a.flag1 = fl + m->V;
     a.list0 = fl + 2 * static_cast<size_t>(m->V);
     a.list1 = fl + 3 * static_cast<size_t>(m->V);
-    a.cnt = c.take<int32_t>(2);
+    int32_t *cnt = c.take<int32_t>(4);
     a.stats = tstats;
     const unsigned zg = static_cast<unsigned>(std::min<int64_t>(8192, ceil_div(static_cast<int64_t>(m->V) * m->dim, 256)));
     k_zero_u64_range<<<zg, 256, 0, s>>>(a.d0, static_cast<int64_t>(m->V) * m->dim);
     k_zero_u64_range<<<zg, 256, 0, s>>>(a.d1, static_cast<int64_t>(m->V) * m->dim);
     k_zero_i32_range<<<static_cast<unsigned>(ceil_div(2LL * m->V, 256)), 256, 0, s>>>(fl, 2LL * m->V);
-    k_reset_counts<<<1, 64, 0, s>>>(a.cnt);
+    k_reset_counts<<<1, 64, 0, s>>>(cnt);
     if (n_tokens <= 0) return W2V_OK;
     k_scan_kept<<<1, kScanThreads, 0, s>>>(b.doc_kept, a.n_docs, kept_off);
     W2V_LAUNCH_CHECK("sync setup");
@@ -237,14 +291,13 @@ int run_train_sync(const w2v_model *m, const w2v_params *p, const SampleBufs &b,
     const int64_t kept = tot[2];
     SyncFn fn = pick_sync(m->dim);
     const unsigned ag = static_cast<unsigned>(std::max(1, device_cu_count() * 4));
-    for (int64_t lo = 0; lo < kept; lo += p->sync_batch) {
+    int parity = 0;
+    for (int64_t lo = 0; lo < kept; lo += p->sync_batch, parity ^= 1) {
         a.c_lo = lo;
         a.c_hi = std::min<int64_t>(kept, lo + p->sync_batch);
-        const unsigned g = static_cast<unsigned>(ceil_div(a.c_hi - a.c_lo, 4));
-        hipLaunchKernelGGL(fn, dim3(g), dim3(256), 0, s, a);
-        k_sync_apply<<<ag, 256, 0, s>>>(m->syn0, m->row_stride, m->dim, a.d0, a.flag0, a.list0, a.cnt);
-        k_sync_apply<<<ag, 256, 0, s>>>(m->syn1, m->row_stride, m->dim, a.d1, a.flag1, a.list1, a.cnt + 1);
-        k_reset_counts<<<1, 64, 0, s>>>(a.cnt);
+        a.cnt = cnt + 2 * parity;
+        hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(a.c_hi - a.c_lo)), dim3(kSyncWaves * kWave), 0, s, a);
+        k_sync_apply<<<ag, 256, 0, s>>>(a, m->syn0, m->syn1, cnt + 2 * (parity ^ 1));
         W2V_LAUNCH_CHECK("sync batch");
     }
     return W2V_OK;

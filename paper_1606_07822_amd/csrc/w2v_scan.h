@@ -1,4 +1,5 @@
-// One-workgroup exclusive prefix sum shared by the per-document and noise-weight scans.
+// One-workgroup exclusive prefix sum shared by the per-document and noise-weight scans, and the one-wavefront
+// search of ascending values.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -51,6 +52,22 @@ __device__ int64_t block_exclusive_scan(const In *__restrict__ in, int64_t n, Ou
         carry += step;
     }
     return carry;
+}
+
+// First index in [lo, hi) at which pred (true up to some index, false from there on) is false, by one
+// wavefront: 64 probes a step.
+template <class F>
+__device__ __forceinline__ int32_t wave_partition_point(int32_t lo, int32_t hi, F pred) {
+    const int lane = lane_id();
+    while (lo < hi) {
+        const int32_t step = (hi - lo + kWave - 1) / kWave;
+        const int64_t at = lo + static_cast<int64_t>(lane + 1) * step - 1;
+        const int n = __popcll(__ballot(at < hi && pred(static_cast<int32_t>(at))));
+        const int64_t end = lo + static_cast<int64_t>(n + 1) * step - 1;   // the first failing probe, if there is one
+        lo += n * step;
+        hi = end < hi ? static_cast<int32_t>(end) : hi;
+    }
+    return lo;
 }
 
 }  // namespace w2v

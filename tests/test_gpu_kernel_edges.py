@@ -94,3 +94,32 @@ def test_narrow_rows_single_worker_matches_oracle(w2v, name, sample, dim, win, w
     g0, g1 = (t.cpu().numpy() for t in model.vectors())
     assert row_rel_err(g0, a0) <= 1e-4
     assert row_rel_err(g1[:s.voc.V - 1], a1) <= 1e-4
+
+
+# ------------------------------------------------------------- synchronous mode
+# Every variant (rows of up to 64, 128, 256, 320, 512 and 1024 floats) at both ends of its range, windows that
+# take one group of words and several (12, 8 or 4 words a group), single-word windows, batches of one and of
+# more than one centre, and a last batch that is not full. The sums are exact on both sides; the bar is the
+# other synchronous tests'.
+@pytest.mark.parametrize("dim,win,batch", [(1, 1, 1), (64, 6, 100), (65, 10, 256), (128, 7, 33), (129, 4, 256),
+                                           (256, 10, 64), (257, 5, 256), (320, 2, 100), (321, 3, 64), (512, 10, 128),
+                                           (513, 2, 64), (1024, 9, 50)])
+def test_sync_variants_match_oracle(w2v, dim, win, batch):
+    log(f"sync dim={dim} window={win} batch={batch}")
+    s = oracle_side("tiny_sg_v1k_d50")
+    voc = w2v.build_vocab(to_dev(s.tok), s.w.vocab, s.w.min_count)
+    tree = w2v.build_huffman(voc.vocab_counts)
+    tv = s.tv[:1501]
+    syn0, syn1 = synth.init_weights(s.voc.V, dim, syn1_scale=0.5 / dim)
+    a0, a1 = syn0.copy(), syn1.copy()
+    op = oracle.params(s.voc.V, dim, window=win, sample=1e-3, train_words=s.voc.train_words,
+                       corpus_tokens=s.tv.size, sync_batch=batch)
+    ost = oracle.train_sync(a0, a1, s.tree, tv, op, n_batches=-1)
+    model = w2v.make_model(syn0, syn1, voc, tree, stride=(dim + 3) // 4 * 4, pad_value=float("nan"))
+    p = w2v.Params(window=win, sample=1e-3, corpus_tokens=s.tv.size, mode=1, sync_batch=batch,
+                   cache_k=0)
+    st = w2v.train_hs_epoch(model, to_dev(tv), p).cpu().numpy()
+    assert list(st) == list(ost)
+    g0, g1 = (t.cpu().numpy() for t in model.vectors())
+    assert row_rel_err(g0, a0) <= 1e-4
+    assert row_rel_err(g1[:s.voc.V - 1], a1) <= 1e-4
