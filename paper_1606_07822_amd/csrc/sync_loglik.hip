@@ -306,12 +306,6 @@ int run_train_sync(const w2v_model *m, const w2v_params *p, const SampleBufs &b,
 // ------------------------------------------------------------- log-likelihood
 namespace {
 
-// log sigmoid(u) = min(u, 0) - log(1 + exp(-|u|)): the same operations as the two one-sided forms, without
-// a branch (lanes of both signs would run both sides)
-__device__ __forceinline__ double log_sigmoid(double u) {
-    return fmin(u, 0.0) - log1p(exp(-fabs(u)));
-}
-
 // Held-out evaluation work units: kLLSeg consecutive kept centres of a document, one wavefront each.
 // Short units keep the read-only walk's latency spread over many wavefronts (8: 4.2 ms for the 1e6-token
 // held-out corpus at V = 1M, d = 300; the training kernel's 128-centre units: 8.4 ms).
@@ -337,177 +331,304 @@ struct LLArgs {
     int64_t *unit_terms;    // CBOW: centres with a window, per unit
 };
 
-// One wavefront per work unit (a fixed assignment, so the sums are the same from run to run).
-// Per centre the path is walked once for a group of up to G window words: four node rows at a
-// time (the next four loaded while the current ones are used), the G x 4 dot products reduced
-// four at a time; lane n collects the dot products of path node n, and takes the log-sigmoids
-// of its node for every pair of the group in fp64.
-template <int NE, int G>
-__global__ __launch_bounds__(256) void k_loglik(LLArgs a) {
+// The centres of a work unit, one a lane, and the words around them.
+constexpr int kLLReach = 10;   // the widest window
+struct LLUnit {
+    int64_t base;
+    int nk, j0, n;   // kept words of the document, the unit's first centre and number of centres
+    int eff, len, po, sid;   // lane c: half-width, path length and offset of centre j0 + c; lane l: word at j0 - kLLReach + l
+    int code_lo, code_hi;
+};
+
+__device__ __forceinline__ LLUnit ll_unit(const LLArgs &a, int64_t u, int lane) {
+    LLUnit r{};
+    const int64_t d = u / a.segs_per_doc;
+    r.nk = a.doc_kept[d];
+    r.j0 = static_cast<int>(u - d * a.segs_per_doc) * kLLSeg;
+    r.n = min(kLLSeg, r.nk - r.j0);
+    r.base = d * a.doc_len;
+    if (r.n <= 0) return r;
+    const int pos = r.j0 - kLLReach + lane;
+    r.sid = lane < kLLSeg + 2 * kLLReach && pos >= 0 && pos < r.nk ? a.kept_vid[r.base + pos] : 0;
+    if (lane < r.n) {
+        const int v = a.kept_vid[r.base + r.j0 + lane];
+        r.eff = static_cast<int>(a.kept_meta[r.base + r.j0 + lane] >> 16);
+        r.len = a.codelen[v];
+        r.po = a.point_off[v];
+        const uint64_t code = a.code[v];
+        r.code_lo = static_cast<int>(code);
+        r.code_hi = static_cast<int>(code >> 32);
+    }
+    return r;
+}
+
+// Centre c's path: lane l, its l-th node.
+__device__ __forceinline__ int ll_path(const LLArgs &a, const LLUnit &r, int c, int lane) {
+    const int len = __builtin_amdgcn_readlane(r.len, c);
+    return lane < len ? a.points[__builtin_amdgcn_readlane(r.po, c) + lane] : 0;
+}
+
+__device__ __forceinline__ uint64_t ll_code(const LLUnit &r, int c) {
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(r.code_lo, c)) |
+           static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(r.code_hi, c))) << 32;
+}
+
+// Sum of log sigmoids as one logarithm: log sigmoid(u) = min(u, 0) - log(1 + exp(-|u|)), and the logarithms of
+// many factors in (1, 2] are the logarithm of their product (a lane takes at most 5 groups x 4 blocks of nodes x
+// kLLSeg centres = 160 factors, so the product stays below 2^160). Each factor adds 2^-53 to the sum's absolute
+// error, as its own logarithm would; below 2^-10, where that would show beside the term itself, the term is
+// summed directly, by five terms of its series (relative error below 2^-52).
+struct LogSigmoidSum {
+    double sum = 0.0, product = 1.0;
+    __device__ __forceinline__ void add(double u, bool live) {
+        const double e = exp(-fabs(u));
+        const double series = e * fma(e, fma(e, fma(e, fma(e, 0.2, -0.25), 1.0 / 3.0), -0.5), 1.0);
+        const bool small = e < 0x1p-10;
+        sum += live ? fmin(u, 0.0) - (small ? series : 0.0) : 0.0;
+        product *= live && !small ? 1.0 + e : 1.0;
+    }
+    __device__ __forceinline__ double total() const { return sum - log(product); }
+};
+
+// Columns c0 + 64 t + 4 (lane / 4) .. + 3 of the row that this lane's place in its quad takes, zeros past dim: four
+// rows a load, in the form that mfma4 multiplies. The first FULL tiles lie within the row.
+template <int FULL, int NE>
+__device__ __forceinline__ void load_quad_rows(f4 (&r)[NE], const float *m, int stride, int dim, int c0, int row, int lane) {
+    const float *p = m + static_cast<int64_t>(row) * stride + c0 + (lane >> 2) * 4;
+#pragma unroll
+    for (int t = 0; t < NE; ++t) {
+        if (t < FULL) {
+            r[t] = *reinterpret_cast<const f4 *>(p + t * kWave);
+        } else {
+            const int col = c0 + t * kWave + (lane >> 2) * 4;
+            r[t] = *reinterpret_cast<const f4 *>(p + (col < dim ? t * kWave : -c0));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) r[t][i] = col + i < dim ? r[t][i] : 0.0f;
+        }
+    }
+}
+
+// One wavefront per work unit (a fixed assignment, so the sums are the same from run to run), in steps of one
+// centre, up to 4 G of its window words and up to 32 of its nodes: four node rows at a time, the next four loaded
+// meanwhile, their products with four words in 32 bits on the matrix cores; then lane 16 i + n holds word i's
+// product with node n (and 16 + n), and all lanes take their log sigmoids in 64 bits at once, while the next
+// step's window rows and first nodes are on their way. A row is read four columns a lane, four rows an
+// instruction. Rows above 512 floats (PANELS) go in panels of 512 columns whose products are added.
+// What bounds it is the latency of the rows: with a lane per column, vector dot products reduced across lanes and
+// the log sigmoids of one word at a time (18 of 64 lanes) the 1e6-token held-out corpus took 3.97 ms at V = 1M,
+// d = 300, this 2.05 ms (three
+// wavefronts per SIMD, forced: two, without a spilled register, take 2.9 ms; twelve words a step 2.15).
+template <int NE, int G, int FULL, bool PANELS = false>
+__global__ __launch_bounds__(256, NE <= 5 ? 3 : 2) void k_loglik(LLArgs a) {
     const int lane = lane_id();
     const int64_t wave0 = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) / kWave;
     const int64_t nwaves = static_cast<int64_t>(gridDim.x) * blockDim.x / kWave;
+    const int row = lane >> 4;
     for (int64_t u = wave0; u < a.n_units; u += nwaves) {
-        const int64_t d = u / a.segs_per_doc;
-        const int nk = a.doc_kept[d];
-        const int j0 = static_cast<int>(u - d * a.segs_per_doc) * kLLSeg;
-        const int j1 = min(nk, j0 + kLLSeg);
-        const int64_t base = d * a.doc_len;
-        double acc = 0.0;
+        const LLUnit r = ll_unit(a, u, lane);
+        LogSigmoidSum acc;
         int64_t nodes = 0;
-        for (int j = j0; j < j1; ++j) {
-            const int v = a.kept_vid[base + j];
-            const int eff = static_cast<int>(a.kept_meta[base + j] >> 16);
-            const int clo = max(0, j - eff), chi = min(nk - 1, j + eff);
-            const int P = chi - clo;
-            const int len = a.codelen[v];
-            const uint64_t code = a.code[v];
-            const int my_pt = (lane < len) ? a.points[a.point_off[v] + lane] : 0;
-            // lane q: the q-th window word (centre excluded)
-            const int cq = clo + lane + ((clo + lane >= j) ? 1 : 0);
-            const int my_w = (lane < P) ? a.kept_vid[base + cq] : 0;
-            const double sign = ((code >> min(lane, 63)) & 1ull) ? -1.0 : 1.0;
-            for (int g0 = 0; g0 < P; g0 += G) {
-                const int nx = min(G, P - g0);
-                float x[G][NE], mine[G];
+        // the step: centre c, its path and code, the window's start and words, words g0 .., nodes n0 ..
+        int c = -1, pt = 0, len = 0, clo = 0, P = 0, g0 = 0, n0 = 0;
+        int pt_next = r.n > 0 ? ll_path(a, r, 0, lane) : 0;
+        f4 x[G][NE], y[NE];
+        auto next_step = [&]() {   // false after the last one
+            if (n0 + 32 < len) {
+                n0 += 32;
+                return true;
+            }
+            n0 = 0;
+            g0 += 4 * G;
+            while (g0 >= P) {
+                if (++c >= r.n) return false;
+                const int eff = __builtin_amdgcn_readlane(r.eff, c);
+                clo = max(0, r.j0 + c - eff);
+                P = min(r.nk - 1, r.j0 + c + eff) - clo;
+                len = __builtin_amdgcn_readlane(r.len, c);
+                g0 = 0;
+                pt = pt_next;
+                pt_next = ll_path(a, r, min(c + 1, r.n - 1), lane);
+                nodes += static_cast<int64_t>(P) * len;
+            }
+            return true;
+        };
+        auto load_words = [&](int c0) {
 #pragma unroll
-                for (int p = 0; p < G; ++p) {
-                    const int w = __builtin_amdgcn_readlane(my_w, min(g0 + p, kWave - 1));
-                    buf_load_row<NE>(x[p], row_rsrc(const_cast<float *>(a.syn0), p < nx ? w : 0, a.stride,
-                                                    p < nx ? a.dim * 4 : 0), lane);
-                    mine[p] = 0.0f;
+            for (int g = 0; g < G; ++g) {
+                if (g0 + 4 * g < P) {
+                    const int q = g0 + 4 * g + (lane & 3);   // past the window: any row
+                    const int k = clo + q - r.j0 + kLLReach + (clo + q >= r.j0 + c ? 1 : 0);
+                    const int w = __shfl(r.sid, k, kWave);
+                    load_quad_rows<FULL>(x[g], a.syn0, a.stride, a.dim, c0, q < P ? w : 0, lane);
                 }
-                float y[4][NE], yn[4][NE];
+            }
+        };
+        auto load_nodes = [&](f4(&to)[NE], int first, int c0) {
+            const int n = first + (lane & 3);                // past the path: any row
+            const int nd = __shfl(pt, min(n, kWave - 1), kWave);
+            load_quad_rows<FULL>(to, a.syn1, a.stride, a.dim, c0, n < len ? nd : 0, lane);
+        };
+        bool more = next_step();
+        if (more) {
+            load_words(0);
+            load_nodes(y, 0, 0);
+        }
+        while (more) {
+            float z[G][2];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int n = __builtin_amdgcn_readlane(my_pt, min(r, kWave - 1));
-                    buf_load_row<NE>(y[r], row_rsrc(const_cast<float *>(a.syn1), r < len ? n : 0, a.stride,
-                                                    r < len ? a.dim * 4 : 0), lane);
+            for (int g = 0; g < G; ++g) z[g][0] = z[g][1] = 0.0f;
+            const int end = min(len, n0 + 32), nx = min(4 * G, P - g0);
+            for (int c0 = 0; c0 < (PANELS ? a.dim : 1); c0 += NE * kWave) {
+                if (PANELS && c0 > 0) {
+                    load_words(c0);
+                    load_nodes(y, n0, c0);
                 }
-                for (int c0 = 0; c0 < len; c0 += 4) {
+                for (int n = n0; n < end; n += 4) {
+                    f4 yn[NE];
+                    load_nodes(yn, n + 4, c0);
+                    const int k = (n - n0) >> 2;
+                    const bool here = ((lane >> 2) & 3) == (k & 3), low = k < 4;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int c = c0 + 4 + r;
-                        const int n = __builtin_amdgcn_readlane(my_pt, min(c, kWave - 1));
-                        buf_load_row<NE>(yn[r], row_rsrc(const_cast<float *>(a.syn1), c < len ? n : 0, a.stride,
-                                                         c < len ? a.dim * 4 : 0), lane);
-                    }
+                    for (int g = 0; g < G; ++g) {
+                        if (4 * g < nx) {
+                            f4 d = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                    for (int p = 0; p < G; ++p) {
-                        if (p < nx) {
-                            const float z = reduce4(dot_partial<NE>(x[p], y[0]), dot_partial<NE>(x[p], y[1]),
-                                                    dot_partial<NE>(x[p], y[2]), dot_partial<NE>(x[p], y[3]));
+                            for (int t = 0; t < NE; ++t)
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) {
-                                const float zr = __builtin_bit_cast(
-                                    float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, z), 16 * r));
-                                mine[p] = (lane == c0 + r) ? zr : mine[p];
-                            }
+                                for (int i = 0; i < 4; ++i) d = mfma4(x[g][t][i], y[t][i], d);
+                            const float sum = block_sum(d);
+                            z[g][0] += here && low ? sum : 0.0f;
+                            z[g][1] += here && !low ? sum : 0.0f;
                         }
                     }
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-#pragma unroll
-                        for (int i = 0; i < NE; ++i) y[r][i] = yn[r][i];
+                    for (int t = 0; t < NE; ++t) y[t] = yn[t];
                 }
-#pragma unroll
-                for (int p = 0; p < G; ++p)
-                    if (p < nx && lane < len) acc += log_sigmoid(sign * static_cast<double>(mine[p]));
             }
-            nodes += static_cast<int64_t>(P) * len;
+            const uint64_t code = ll_code(r, c);
+            const int first = n0, to = end;
+            more = next_step();
+            if (more) {
+                load_words(0);
+                load_nodes(y, n0, 0);
+            }
+            // (one group of words and sixteen nodes after another: the 64-bit work of all of them at once would
+            // take a third of the registers)
+#pragma unroll 1
+            for (int half = 0; half < 2 && first + 16 * half < to; ++half) {
+                const int n = first + 16 * half + (lane & 15);
+                const bool minus = (code >> min(n, 63)) & 1ull;
+#pragma unroll 1
+                for (int g = 0; 4 * g < nx; ++g) {
+                    float zg = half ? z[0][1] : z[0][0];
+#pragma unroll
+                    for (int k = 1; k < G; ++k) zg = g == k ? (half ? z[k][1] : z[k][0]) : zg;
+                    acc.add(static_cast<double>(minus ? -zg : zg), n < to && 4 * g + row < nx);
+                }
+            }
         }
-        acc = wave_sum(acc);
+        const double sum = wave_sum(acc.total());
         if (lane == 0) {
-            a.unit_ll[u] = acc;
+            a.unit_ll[u] = sum;
             a.unit_nodes[u] = nodes;
         }
     }
 }
 
-// CBOW: one wavefront per work unit; per centre with a window, h = (sum of the window rows in
-// ascending window order, fp64) / P, then one walk of the centre's path with fp64 dot products
-// (lane n keeps the dot product of path node n and takes its log-sigmoid).
+// CBOW: one wavefront per work unit; per centre with a window, h = (sum of the window rows in ascending window
+// order, fp64) / P, then one walk of the centre's path with fp64 dot products, four nodes at a time (the next
+// four rows loaded meanwhile) and reduced together; lane 16 r + k keeps node 4 k + r. Node after node, each with
+// a sum over the wavefront of its own, it took 2.11 ms for the 1e6-token held-out corpus at V = 100K, d = 300,
+// this 1.3 (four
+// wavefronts per SIMD; 1.7 with three).
 template <int NE>
-__global__ __launch_bounds__(256) void k_loglik_cbow(LLArgs a) {
+__global__ __launch_bounds__(256, NE <= 5 ? 4 : (NE <= 8 ? 3 : 2)) void k_loglik_cbow(LLArgs a) {
     const int lane = lane_id();
     const int64_t wave0 = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) / kWave;
     const int64_t nwaves = static_cast<int64_t>(gridDim.x) * blockDim.x / kWave;
+    auto load = [&](float(&to)[NE], const float *m, int row, bool in) {
+        buf_load_row<NE>(to, row_rsrc(const_cast<float *>(m), in ? row : 0, a.stride, in ? a.dim * 4 : 0), lane);
+    };
     for (int64_t u = wave0; u < a.n_units; u += nwaves) {
-        const int64_t d = u / a.segs_per_doc;
-        const int nk = a.doc_kept[d];
-        const int j0 = static_cast<int>(u - d * a.segs_per_doc) * kLLSeg;
-        const int j1 = min(nk, j0 + kLLSeg);
-        const int64_t base = d * a.doc_len;
-        double acc = 0.0;
+        const LLUnit r = ll_unit(a, u, lane);
+        LogSigmoidSum acc;
         int64_t nodes = 0, terms = 0;
-        for (int j = j0; j < j1; ++j) {
-            const int v = a.kept_vid[base + j];
-            const int eff = static_cast<int>(a.kept_meta[base + j] >> 16);
-            const int clo = max(0, j - eff), chi = min(nk - 1, j + eff);
+        int pt_next = r.n > 0 ? ll_path(a, r, 0, lane) : 0;
+        for (int c = 0; c < r.n; ++c) {
+            const int j = r.j0 + c;
+            const int eff = __builtin_amdgcn_readlane(r.eff, c), len = __builtin_amdgcn_readlane(r.len, c);
+            const uint64_t code = ll_code(r, c);
+            const int my_pt = pt_next;
+            pt_next = ll_path(a, r, min(c + 1, r.n - 1), lane);
+            const int clo = max(0, j - eff), chi = min(r.nk - 1, j + eff);
             const int P = chi - clo;
             if (P == 0) continue;
-            const int len = a.codelen[v];
-            const uint64_t code = a.code[v];
-            const int my_pt = (lane < len) ? a.points[a.point_off[v] + lane] : 0;
-            const int cq = clo + lane + ((clo + lane >= j) ? 1 : 0);
-            const int my_w = (lane < P) ? a.kept_vid[base + cq] : 0;
+            float y[4][NE], yn[4][NE];
+            auto load_nodes = [&](float(&to)[4][NE], int n0) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    load(to[i], a.syn1, __builtin_amdgcn_readlane(my_pt, min(n0 + i, kWave - 1)), n0 + i < len);
+            };
+            load_nodes(y, 0);
             double h[NE];
 #pragma unroll
             for (int i = 0; i < NE; ++i) h[i] = 0.0;
-            for (int q = 0; q < P; ++q) {
-                float x[NE];
-                buf_load_row<NE>(x, row_rsrc(const_cast<float *>(a.syn0), __builtin_amdgcn_readlane(my_w, q),
-                                             a.stride, a.dim * 4), lane);
+            for (int q = 0; q < P; q += 4) {
+                float x[4][NE];
 #pragma unroll
-                for (int i = 0; i < NE; ++i) h[i] += static_cast<double>(x[i]);
+                for (int k = 0; k < 4; ++k) {
+                    const int pos = clo + q + k + (clo + q + k >= j ? 1 : 0);
+                    load(x[k], a.syn0, __builtin_amdgcn_readlane(r.sid, min(pos - r.j0 + kLLReach, kWave - 1)), q + k < P);
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int i = 0; i < NE; ++i) h[i] += static_cast<double>(x[k][i]);
             }
 #pragma unroll
             for (int i = 0; i < NE; ++i) h[i] = h[i] / static_cast<double>(P);
             double mine = 0.0;
-            for (int c = 0; c < len; ++c) {
-                float y[NE];
-                buf_load_row<NE>(y, row_rsrc(const_cast<float *>(a.syn1), __builtin_amdgcn_readlane(my_pt, c),
-                                             a.stride, a.dim * 4), lane);
-                double z = 0.0;
+            for (int n0 = 0; n0 < len; n0 += 4) {
+                load_nodes(yn, n0 + 4);
+                double z[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                for (int i = 0; i < NE; ++i) z += h[i] * static_cast<double>(y[i]);
-                z = wave_sum(z);
-                mine = (lane == c) ? z : mine;
+                for (int i = 0; i < NE; ++i)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) z[k] += h[i] * static_cast<double>(y[k][i]);
+                const double s = reduce4(z[0], z[1], z[2], z[3]);
+                mine = (lane & 15) == (n0 >> 2) ? s : mine;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int i = 0; i < NE; ++i) y[k][i] = yn[k][i];
             }
-            const double sign = ((code >> min(lane, 63)) & 1ull) ? -1.0 : 1.0;
-            if (lane < len) acc += log_sigmoid(sign * mine);
+            const int n = 4 * (lane & 15) + (lane >> 4);
+            acc.add(((code >> n) & 1ull) ? -mine : mine, n < len);
             nodes += len;
             terms += 1;
         }
-        acc = wave_sum(acc);
+        const double sum = wave_sum(acc.total());
         if (lane == 0) {
-            a.unit_ll[u] = acc;
+            a.unit_ll[u] = sum;
             a.unit_nodes[u] = nodes;
             a.unit_terms[u] = terms;
         }
     }
 }
 
-// fixed-order sum of the work units' partials (terms: optional)
-__global__ __launch_bounds__(1024) void k_sum_docs(const double *__restrict__ ll, const int64_t *__restrict__ nodes,
-                                                   const int64_t *__restrict__ terms, int64_t n,
-                                                   double *__restrict__ out_ll, int64_t *__restrict__ out_nodes,
-                                                   int64_t *__restrict__ out_terms) {
-    __shared__ double sl[1024];
-    __shared__ int64_t sn[1024];
-    __shared__ int64_t st_[1024];
-    double a = 0.0;
-    int64_t b = 0, t = 0;
-    for (int64_t i = threadIdx.x; i < n; i += 1024) {
-        a += ll[i];
-        b += nodes[i];
-        if (terms) t += terms[i];
-    }
+// Fixed-order sum of the work units' partials (terms: optional) in two passes: each workgroup adds the units of
+// its stretch, in place (its first unit takes the sum), then one workgroup adds the stretches (at most one a
+// thread). One workgroup over all units took 58 us for 125,000.
+constexpr int kSumThreads = 1024;
+__device__ __forceinline__ void block_sum3(double &a, int64_t &b, int64_t &t) {
+    __shared__ double sl[kSumThreads];
+    __shared__ int64_t sn[kSumThreads];
+    __shared__ int64_t st_[kSumThreads];
     sl[threadIdx.x] = a;
     sn[threadIdx.x] = b;
     st_[threadIdx.x] = t;
     __syncthreads();
-    for (int st = 512; st > 0; st >>= 1) {
+    for (int st = kSumThreads / 2; st > 0; st >>= 1) {
         if (threadIdx.x < st) {
             sl[threadIdx.x] += sl[threadIdx.x + st];
             sn[threadIdx.x] += sn[threadIdx.x + st];
@@ -515,23 +636,56 @@ __global__ __launch_bounds__(1024) void k_sum_docs(const double *__restrict__ ll
         }
         __syncthreads();
     }
+    a = sl[0];
+    b = sn[0];
+    t = st_[0];
+}
+
+__global__ __launch_bounds__(kSumThreads) void k_sum_units(double *ll, int64_t *nodes, int64_t *terms, int64_t n,
+                                                           int64_t stretch) {
+    const int64_t lo = blockIdx.x * stretch, hi = min(n, lo + stretch);
+    double a = 0.0;
+    int64_t b = 0, t = 0;
+    for (int64_t i = lo + threadIdx.x; i < hi; i += kSumThreads) {
+        a += ll[i];
+        b += nodes[i];
+        if (terms) t += terms[i];
+    }
+    block_sum3(a, b, t);
     if (threadIdx.x == 0) {
-        *out_ll = sl[0];
-        *out_nodes = sn[0];
-        *out_terms = st_[0];
+        ll[lo] = a;
+        nodes[lo] = b;
+        if (terms) terms[lo] = t;
+    }
+}
+
+__global__ __launch_bounds__(kSumThreads) void k_sum_stretches(const double *__restrict__ ll,
+                                                               const int64_t *__restrict__ nodes,
+                                                               const int64_t *__restrict__ terms, int64_t n,
+                                                               int64_t stretch, double *__restrict__ out_ll,
+                                                               int64_t *__restrict__ out_nodes,
+                                                               int64_t *__restrict__ out_terms) {
+    const int64_t i = threadIdx.x * stretch;
+    double a = i < n ? ll[i] : 0.0;
+    int64_t b = i < n ? nodes[i] : 0, t = terms && i < n ? terms[i] : 0;
+    block_sum3(a, b, t);
+    if (threadIdx.x == 0) {
+        *out_ll = a;
+        *out_nodes = b;
+        *out_terms = t;
     }
 }
 
 using LLFn = void (*)(LLArgs);
-// G window words per path walk: all of a window of half-width 5 for rows of up to 320 floats.
+// 4 G window words per step: all of a window of half-width 5 for rows of up to 128 floats, eight words above.
 LLFn pick_ll(int dim) {
     const int ne = (dim + kWave - 1) / kWave;
-    if (ne <= 1) return k_loglik<1, 10>;
-    if (ne <= 2) return k_loglik<2, 10>;
-    if (ne <= 4) return k_loglik<4, 10>;
-    if (ne <= 5) return k_loglik<5, 8>;   // 159 VGPRs: 3 waves per SIMD (10 words: 171, 2 waves)
-    if (ne <= 8) return k_loglik<8, 4>;
-    return k_loglik<16, 2>;
+    if (ne <= 1) return k_loglik<1, 3, 0>;
+    if (ne <= 2) return k_loglik<2, 3, 1>;
+    if (ne <= 4) return k_loglik<4, 2, 2>;
+    if (ne <= 5) return k_loglik<5, 2, 4>;
+    if (ne <= 8) return k_loglik<8, 2, 5>;
+    return k_loglik<8, 2, 0, true>;
 }
 
 LLFn pick_ll_cbow(int dim) {
@@ -590,9 +744,13 @@ int run_loglik(const w2v_model *m, const w2v_params *p, const SampleBufs &b, int
         const unsigned grid = static_cast<unsigned>(std::min<int64_t>(ceil_div(a.n_units, 4), INT32_MAX));
         hipLaunchKernelGGL(cbow ? pick_ll_cbow(m->dim) : pick_ll(m->dim), dim3(grid), dim3(256), 0, s, a);
         W2V_LAUNCH_CHECK("k_loglik");
-        k_sum_docs<<<1, 1024, 0, s>>>(a.unit_ll, a.unit_nodes, cbow ? a.unit_terms : nullptr, a.n_units, out,
-                                      out_nt, out_nt + 1);
-        W2V_LAUNCH_CHECK("k_sum_docs");
+        int64_t *terms = cbow ? a.unit_terms : nullptr;
+        const int64_t stretch = std::max<int64_t>(kSumThreads, ceil_div(a.n_units, kSumThreads));
+        k_sum_units<<<static_cast<unsigned>(ceil_div(a.n_units, stretch)), kSumThreads, 0, s>>>(
+            a.unit_ll, a.unit_nodes, terms, a.n_units, stretch);
+        k_sum_stretches<<<1, kSumThreads, 0, s>>>(a.unit_ll, a.unit_nodes, terms, a.n_units, stretch, out, out_nt,
+                                                  out_nt + 1);
+        W2V_LAUNCH_CHECK("k_sum_units");
     }
     double hll = 0.0;
     int64_t nt[2] = {0, 0};

@@ -176,6 +176,63 @@ __device__ __forceinline__ float dot_partial(const float (&x)[NE], const float (
     return s;
 }
 
+// The same for doubles.
+__device__ __forceinline__ void swap32(double &a, double &b) {
+    float al = __int_as_float(__double2loint(a)), ah = __int_as_float(__double2hiint(a));
+    float bl = __int_as_float(__double2loint(b)), bh = __int_as_float(__double2hiint(b));
+    swap32(al, bl);
+    swap32(ah, bh);
+    a = __hiloint2double(__float_as_int(ah), __float_as_int(al));
+    b = __hiloint2double(__float_as_int(bh), __float_as_int(bl));
+}
+__device__ __forceinline__ void swap16(double &a, double &b) {
+    float al = __int_as_float(__double2loint(a)), ah = __int_as_float(__double2hiint(a));
+    float bl = __int_as_float(__double2loint(b)), bh = __int_as_float(__double2hiint(b));
+    swap16(al, bl);
+    swap16(ah, bh);
+    a = __hiloint2double(__float_as_int(ah), __float_as_int(al));
+    b = __hiloint2double(__float_as_int(bh), __float_as_int(bl));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_row(double v) {
+    return __hiloint2double(__float_as_int(dpp_row<CTRL>(__int_as_float(__double2hiint(v)))),
+                            __float_as_int(dpp_row<CTRL>(__int_as_float(__double2loint(v)))));
+}
+__device__ __forceinline__ double reduce4(double a0, double a1, double a2, double a3) {
+    swap32(a0, a2);
+    double r = a0 + a2;
+    swap32(a1, a3);
+    double q = a1 + a3;
+    swap16(r, q);
+    r += q;
+    r += dpp_row<0xB1>(r);
+    r += dpp_row<0x4E>(r);
+    r += dpp_row<0x141>(r);
+    r += dpp_row<0x140>(r);
+    return r;
+}
+
+// ------------------------------------------------------------------ 4 x 4 blocks on the matrix cores
+// v_mfma_f32_4x4x1 adds one product to each of sixteen 4 x 4 blocks: lane 4b+i of A and of B is row i (column i)
+// of block b, register i of lane 4b+j of the result is element (i, j).
+using f4 = float __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f4 mfma4(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0); }
+
+// Sum over the sixteen blocks: lane 16 i + 4 k + j (any k) holds element (i, j).
+__device__ __forceinline__ float block_sum(f4 v) {
+    float a0 = v[0], a1 = v[1], a2 = v[2], a3 = v[3];
+    swap32(a0, a2);
+    float r = a0 + a2;
+    swap32(a1, a3);
+    float q = a1 + a3;
+    swap16(r, q);
+    r += q;
+    r += dpp_row<0x124>(r);   // row_ror:4
+    r += dpp_row<0x128>(r);   // row_ror:8
+    return r;
+}
+
 // Full-wave sum, result in every lane.
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

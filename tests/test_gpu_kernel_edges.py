@@ -123,3 +123,39 @@ def test_sync_variants_match_oracle(w2v, dim, win, batch):
     g0, g1 = (t.cpu().numpy() for t in model.vectors())
     assert row_rel_err(g0, a0) <= 1e-4
     assert row_rel_err(g1[:s.voc.V - 1], a1) <= 1e-4
+
+
+# ------------------------------------------------------------- log-likelihood
+# Rows that end inside, at and just past a 64-column tile and a panel of 512 columns, rows that are not a
+# multiple of four floats (with NaN behind them), windows that take one and several groups of words, documents
+# shorter and longer than a unit of eight centres, and paths past 32 nodes (a step's limit). The bar is the one
+# of the other log-likelihood tests: 32-bit dot products (skip-gram), 64-bit everything (CBOW).
+@pytest.mark.parametrize("arch", [0, 1])
+@pytest.mark.parametrize("dim,win,doc_len,deep", [(1, 1, 1000, False), (63, 5, 9, False), (64, 4, 1000, False),
+                                                  (66, 10, 1000, True), (128, 5, 7, False), (131, 6, 1000, False),
+                                                  (256, 5, 1000, True), (301, 9, 1000, False), (320, 5, 129, False),
+                                                  (323, 3, 1000, True), (512, 10, 1000, False),
+                                                  (513, 5, 1000, False), (1023, 2, 1000, True), (1024, 4, 100, False)])
+def test_loglik_variants_match_oracle(w2v, arch, dim, win, doc_len, deep):
+    log(f"loglik arch={arch} dim={dim} window={win} doc_len={doc_len} deep={deep}")
+    rng = np.random.default_rng(dim)
+    if deep:   # 45 levels: Fibonacci counts over the last of them
+        fib = [1, 1]
+        while len(fib) < 45:
+            fib.append(fib[-1] + fib[-2])
+        counts = np.array(fib[::-1], np.int64)
+    else:
+        counts = np.sort(rng.integers(5, 5000, 700))[::-1].astype(np.int64)
+    V = counts.size
+    tv = rng.integers(-1, V, 1203).astype(np.int32)
+    otree, tree = oracle.build_huffman(counts), w2v.build_huffman(to_dev(counts))
+    syn0, syn1 = synth.init_weights(V, dim, syn1_scale=3.0 / dim ** 0.5)
+    syn0 = syn0 * np.float32(dim)
+    voc = w2v.Vocab(None, None, to_dev(counts), None, V, int(counts.sum()), None)
+    model = w2v.make_model(syn0, syn1, voc, tree, stride=(dim + 3) // 4 * 4, pad_value=float("nan"))
+    p = w2v.Params(window=win, sample=0.0, seed=9, doc_len=doc_len, arch=arch)
+    s, n, nodes = w2v.hs_loglik(model, to_dev(tv), p)
+    op = oracle.params(V, dim, window=win, sample=0.0, train_words=int(counts.sum()), seed=9, doc_len=doc_len, arch=arch)
+    so, no, nodes_o = oracle.loglik(syn0, syn1, otree, tv, op)
+    assert (n, nodes) == (no, nodes_o)
+    assert abs(s - so) <= (1e-12 if arch == 1 else 1e-6) * abs(so)
