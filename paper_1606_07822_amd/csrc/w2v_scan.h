@@ -11,12 +11,12 @@
 namespace w2v {
 
 // Exclusive prefix sum by one workgroup of kScanThreads threads: out[i] = in[0] + ... + in[i-1] (i < n),
-// summed in int64; returns the sum of all n values (in every thread). Each thread adds kScanPer consecutive
+// summed in int64 (in place if out is in); returns the sum of all n values (in every thread). Each thread adds kScanPer consecutive
 // values per step, so a step covers kScanThreads * kScanPer values with two workgroup barriers.
 constexpr int kScanThreads = 1024;
 constexpr int kScanPer = 16;
 template <typename In, typename Out>
-__device__ int64_t block_exclusive_scan(const In *__restrict__ in, int64_t n, Out *__restrict__ out) {
+__device__ int64_t block_exclusive_scan(const In *in, int64_t n, Out *out) {
     __shared__ int64_t wsum[kScanThreads / kWave];
     const int lane = lane_id(), wid = static_cast<int>(threadIdx.x / kWave);
     int64_t carry = 0;

@@ -159,3 +159,47 @@ def test_loglik_variants_match_oracle(w2v, arch, dim, win, doc_len, deep):
     so, no, nodes_o = oracle.loglik(syn0, syn1, otree, tv, op)
     assert (n, nodes) == (no, nodes_o)
     assert abs(s - so) <= (1e-12 if arch == 1 else 1e-6) * abs(so)
+
+
+# ------------------------------------------------------------- vocabulary
+# One tile of the sort and its edges, several, counts of one digit and of more, every id kept and every id dropped;
+# the long texts' lists (8 million tokens, ids past 36,864): ids that all go to the lists, which then overflow
+# to memory's adds, one id past the bins, a text that is not 16-byte aligned, one of the look-up's size.
+@pytest.mark.parametrize("n,ids,kind,min_count,shift", [
+    (1, 1, "flat", 1, 0), (700, 4096, "flat", 0, 0), (5000, 4097, "zipf", 2, 1), (300_000, 4096, "zipf", 5, 0),
+    (70_000, 8193, "one", 1, 0), (50_000, 3000, "flat", 1000, 0), (8_000_003, 36_865, "zipf", 5, 1),
+    (8_000_001, 50_000, "cold", 3, 0), (8_000_000, 300_007, "zipf", 5, 0), (16_000_002, 1_000_003, "zipf", 2, 2),
+])
+def test_vocab_variants_match_numpy(w2v, n, ids, kind, min_count, shift):
+    log(f"vocab n={n} ids={ids} {kind} min_count={min_count} shift={shift}")
+    rng = np.random.default_rng(n + ids)
+    if kind == "flat":
+        tok = rng.integers(0, ids, n + shift)
+    elif kind == "one":
+        tok = np.where(rng.random(n + shift) < 0.9, ids - 1, rng.integers(0, ids, n + shift))
+    elif kind == "cold":
+        tok = rng.integers(36_864, ids, n + shift)
+    else:
+        tok = np.minimum(np.floor(np.exp(rng.random(n + shift) * np.log(ids + 1.0))) - 1, ids - 1)
+    tok = tok.astype(np.int32)
+    voc = w2v.build_vocab(to_dev(tok)[shift:], ids, min_count)
+    tok = tok[shift:]
+    counts = np.bincount(tok, minlength=ids)
+    order = np.lexsort((np.arange(ids), -counts))
+    order = order[counts[order] >= min_count]
+    i2v = np.full(ids, -1, np.int32)
+    i2v[order] = np.arange(order.size)
+    assert (voc.V, voc.train_words) == (order.size, int(counts[order].sum()))
+    np.testing.assert_array_equal(voc.counts_by_id.cpu().numpy(), counts)
+    np.testing.assert_array_equal(voc.vocab_ids.cpu().numpy(), order)
+    np.testing.assert_array_equal(voc.vocab_counts.cpu().numpy(), counts[order])
+    np.testing.assert_array_equal(voc.id_to_vocab.cpu().numpy(), i2v)
+    np.testing.assert_array_equal(voc.tokens.cpu().numpy(), i2v[tok])
+
+
+def test_vocab_long_text_out_of_range_token_is_an_error(w2v):
+    tok = np.full(8_000_000, 40_000, np.int32)
+    tok[7_999_999] = 50_000
+    with pytest.raises(w2v.W2VError) as e:
+        w2v.build_vocab(to_dev(tok), 50_000, 1)
+    assert e.value.code == w2v.W2V_E_RANGE
