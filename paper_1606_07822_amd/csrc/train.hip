@@ -1248,6 +1248,19 @@ bool defer_variant_for(int arch, int dim, bool buf, int window, size_t cache_k, 
     return 2 * cache_k * v->ls(dim) * sizeof(float) + static_cast<size_t>(v->rec_bytes) + 1024 <= device_max_lds();
 }
 
+// Word-row span at 129 to 256 columns: sixteen wavefronts a workgroup where their centre records (and the stash,
+// if asked for) fit beside the cache. What bounds these rows is the walk's chain of arithmetic and loads, which a fourth wavefront per SIMD
+// covers better than the registers it takes away cost (128 VGPRs, 16 spilled): 1e8 tokens' chunk of 2e7, V = 100K,
+// d = 200: skip-gram 49.3 -> 44.8 ms, CBOW 30.9 -> 27.4. At 300 columns CBOW spills too much (50 -> 90 ms), and
+// skip-gram without the span loses (50.4 -> 53.2).
+bool wide_span_variant(int arch, int dim, bool buf, bool stash, size_t cache_bytes, Variant *v) {
+    if (dim <= 2 * kWave || dim > 4 * kWave) return false;
+    if (arch == 0) *v = variant<4, 10, 16, kPfBuf>(0, true);
+    else *v = buf ? variant<4, 10, 16, kPfBuf>(1, true) : variant<4, 10, 16, kPfAll>(1, true);
+    const size_t stash_bytes = stash ? static_cast<size_t>(v->waves_per_block) * v->ne * kWave * sizeof(float) : 0;
+    return cache_bytes + stash_bytes + static_cast<size_t>(v->rec_bytes) + 1024 <= device_max_lds();
+}
+
 __global__ void k_zero_train(int32_t *queue, unsigned long long *stats) {
     if (threadIdx.x == 0) *queue = 0;
     if (threadIdx.x < 3) stats[threadIdx.x] = 0;
@@ -1332,7 +1345,9 @@ int launch_train_async(TrainArgs a, int arch, int window, hipEvent_t ev0, hipEve
                        int64_t *stats_out, const int64_t *totals) {
     const bool slide = train_slide(arch, a.dim, a.stores_only != 0, a.write_policy, window);
     Variant v;
-    if (slide || !defer_variant_for(arch, a.dim, a.stores_only != 0, window, static_cast<size_t>(a.cache_k), &v))
+    const size_t wide_cache = (a.cache_delta ? 1ull : 2ull) * a.cache_k * lds_stride<4>(a.dim) * sizeof(float);
+    if (slide ? !wide_span_variant(arch, a.dim, a.stores_only != 0, a.span_stash != 0, wide_cache, &v)
+              : !defer_variant_for(arch, a.dim, a.stores_only != 0, window, static_cast<size_t>(a.cache_k), &v))
         v = pick_variant(arch, a.dim, a.stores_only != 0, slide);
     const size_t cache_lds = (a.cache_delta ? 1ull : 2ull) * a.cache_k * v.ls(a.dim) * sizeof(float);
     const size_t stash = span_stash_bytes(v, cache_lds, slide && a.span_stash != 0);

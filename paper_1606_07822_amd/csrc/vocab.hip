@@ -539,7 +539,7 @@ int run_build_vocab(const int32_t *tokens, int64_t n_tokens, int32_t id_space, i
         W2V_LAUNCH_CHECK("k_count_lists");
     } else if (n_tokens > 0) {
         const int cus = device_cu_count();
-        const int64_t want = ceil_div(n_tokens, static_cast<int64_t>(kCountThreads) * 4 * 16);
+        const int64_t want = ceil_div(n_tokens, static_cast<int64_t>(kCountThreads) * 4 * 8);
         const unsigned grid = static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>(want, 1LL * cus)));
         k_count<<<grid, kCountThreads, 0, s>>>(tokens, n_tokens, id_space, counts, scal + 0);
         W2V_LAUNCH_CHECK("k_count");

@@ -96,6 +96,32 @@ def test_narrow_rows_single_worker_matches_oracle(w2v, name, sample, dim, win, w
     assert row_rel_err(g1[:s.voc.V - 1], a1) <= 1e-4
 
 
+# Word rows kept across centres at 129 to 256 floats: the sixteen-wavefront variant, and the twelve-wavefront one
+# where the cache (or the cache and the stash) leaves no room for it.
+@pytest.mark.parametrize("arch", [0, 1])
+@pytest.mark.parametrize("dim,k,stash", [(129, 31, 0), (256, 61, 0), (200, 64, 0), (256, 31, 1), (200, 56, 1)])
+def test_word_span_variants_single_worker_match_oracle(w2v, arch, dim, k, stash):
+    log(f"span arch={arch} dim={dim} k={k} stash={stash}")
+    s = oracle_side("tiny_sg_v1k_d50")
+    voc = w2v.build_vocab(to_dev(s.tok), s.w.vocab, s.w.min_count)
+    tree = w2v.build_huffman(voc.vocab_counts)
+    tv = s.tv[:2003]
+    syn0, syn1 = synth.init_weights(s.voc.V, dim, syn1_scale=0.5 / dim)
+    a0, a1 = syn0.copy(), syn1.copy()
+    op = oracle.params(s.voc.V, dim, window=5, sample=0.0, train_words=s.voc.train_words, arch=arch,
+                       corpus_tokens=s.tv.size, cache_k=k, flush_every=10, order=1)
+    ost = oracle.train(a0, a1, s.tree, tv, op)
+    model = w2v.make_model(syn0, syn1, voc, tree)
+    p = w2v.Params(window=5, sample=0.0, corpus_tokens=s.tv.size, cache_k=k, flush_every=10, workers=1, arch=arch,
+                   write_policy=15, span_stash=stash, stash_from=0)
+    assert w2v.train_word_span(model, p) == 5
+    st = w2v.train_hs_epoch(model, to_dev(tv), p).cpu().numpy()
+    assert list(st) == list(ost)
+    g0, g1 = (t.cpu().numpy() for t in model.vectors())
+    assert row_rel_err(g0, a0) <= 1e-4
+    assert row_rel_err(g1[:s.voc.V - 1], a1) <= 1e-4
+
+
 # ------------------------------------------------------------- synchronous mode
 # Every variant (rows of up to 64, 128, 256, 320, 512 and 1024 floats) at both ends of its range, windows that
 # take one group of words and several (12, 8 or 4 words a group), single-word windows, batches of one and of
