@@ -63,6 +63,7 @@ __global__ __launch_bounds__(kCountThreads) void k_count(const int32_t *__restri
 constexpr int kBuckets = 256;
 constexpr int kListGroups = 256;   // workgroups, and lists
 constexpr int64_t kListTokens = 8'000'000;
+constexpr int64_t kListTokensMost = int64_t(1) << 32;
 
 __global__ __launch_bounds__(kCountThreads) void k_count_lists(const int32_t *__restrict__ tok, int64_t n, int32_t id_space,
                                                                unsigned long long *__restrict__ counts,
@@ -526,8 +527,10 @@ int run_build_vocab(const int32_t *tokens, int64_t n_tokens, int32_t id_space, i
     W2V_LAUNCH_CHECK("zero");
     const int32_t width = static_cast<int32_t>(ceil_div(id_space, kBuckets));
     // lists pay where memory's atomics would take most of the time: texts of some millions of tokens, with ids past
-    // the bins, whose ranges fit LDS and whose remapped text has room for them
-    if (tokens_out && n_tokens >= kListTokens && id_space > kHotBins && width <= kHotBins) {
+    // the bins, whose ranges fit LDS and whose remapped text has room for them; places in the lists' partition (at
+    // most half as many as tokens) are 32 bits
+    if (tokens_out && n_tokens >= kListTokens && n_tokens <= kListTokensMost && id_space > kHotBins &&
+        width <= kHotBins) {
         const int64_t cap = std::min<int64_t>(n_tokens / 2 / kListGroups, INT32_MAX);
         int32_t *parted = tokens_out + n_tokens / 2;
         k_count_lists<<<kListGroups, kCountThreads, 0, s>>>(tokens, n_tokens, id_space, counts, scal + 0, tokens_out, cap,
