@@ -1241,15 +1241,27 @@ constexpr Variant defer_variant() {
     return Variant{k_train_defer<NE, PG, WPB>, WPB, NE, PG, lds_stride<NE>, rb};
 }
 
-bool defer_variant_for(int arch, int dim, bool buf, int window, size_t cache_k, Variant *v) {
+// Sixteen wavefronts a workgroup instead of twelve pay where the text (or the caller's number of workers) gives
+// nearly every compute unit such a workgroup. A shorter text has fewer wavefronts than fit (kMinUnitsPerWave work
+// units each): sixteen to a workgroup then crowd them onto fewer compute units. 2e6 tokens, V = 100K, 1e-3
+// subsampling: d = 200 10.3 ms with twelve, 12.0 with sixteen (CBOW 6.5, 7.3), d = 100 (policy 7) 8.6 with twelve
+// (9.0 with a write per centre), 9.7 with sixteen. 4e6 tokens, 97 % of the compute units: d = 200 13.2 with
+// twelve, 12.4 with sixteen (8.4, 7.5).
+bool fills_chip(int waves_per_block, int workers, int64_t n_units) {
+    const int64_t waves = workers > 0 ? workers : n_units / kMinUnitsPerWave;
+    return waves * 16 >= static_cast<int64_t>(waves_per_block) * device_cu_count() * 15;
+}
+
+bool defer_variant_for(int arch, int dim, bool buf, int window, size_t cache_k, bool fills, Variant *v) {
     if (arch != 0 || !buf || dim > 2 * kWave || window > 5) return false;
     if (dim <= kWave) *v = window <= 2 ? defer_variant<1, 4, 16>() : defer_variant<1, 10, 16>();
-    else *v = window <= 2 ? defer_variant<2, 4, 16>() : defer_variant<2, 10, 16>();
+    else if (fills) *v = window <= 2 ? defer_variant<2, 4, 16>() : defer_variant<2, 10, 16>();
+    else *v = window <= 2 ? defer_variant<2, 4, 12>() : defer_variant<2, 10, 12>();
     return 2 * cache_k * v->ls(dim) * sizeof(float) + static_cast<size_t>(v->rec_bytes) + 1024 <= device_max_lds();
 }
 
-// Word-row span at 129 to 256 columns: sixteen wavefronts a workgroup where their centre records (and the stash,
-// if asked for) fit beside the cache. What bounds these rows is the walk's chain of arithmetic and loads, which a fourth wavefront per SIMD
+// Word-row span at 129 to 256 columns: sixteen wavefronts a workgroup where the text fills the chip with them and
+// their centre records (and the stash, if asked for) fit beside the cache. What bounds these rows is the walk's chain of arithmetic and loads, which a fourth wavefront per SIMD
 // covers better than the registers it takes away cost (128 VGPRs, 16 spilled): 1e8 tokens' chunk of 2e7, V = 100K,
 // d = 200: skip-gram 49.3 -> 44.8 ms, CBOW 30.9 -> 27.4. At 300 columns CBOW spills too much (50 -> 90 ms), and
 // skip-gram without the span loses (50.4 -> 53.2).
@@ -1346,8 +1358,9 @@ int launch_train_async(TrainArgs a, int arch, int window, hipEvent_t ev0, hipEve
     const bool slide = train_slide(arch, a.dim, a.stores_only != 0, a.write_policy, window);
     Variant v;
     const size_t wide_cache = (a.cache_delta ? 1ull : 2ull) * a.cache_k * lds_stride<4>(a.dim) * sizeof(float);
-    if (slide ? !wide_span_variant(arch, a.dim, a.stores_only != 0, a.span_stash != 0, wide_cache, &v)
-              : !defer_variant_for(arch, a.dim, a.stores_only != 0, window, static_cast<size_t>(a.cache_k), &v))
+    const bool fills = fills_chip(16, a.workers, a.n_units);
+    if (slide ? !(fills && wide_span_variant(arch, a.dim, a.stores_only != 0, a.span_stash != 0, wide_cache, &v))
+              : !defer_variant_for(arch, a.dim, a.stores_only != 0, window, static_cast<size_t>(a.cache_k), fills, &v))
         v = pick_variant(arch, a.dim, a.stores_only != 0, slide);
     const size_t cache_lds = (a.cache_delta ? 1ull : 2ull) * a.cache_k * v.ls(a.dim) * sizeof(float);
     const size_t stash = span_stash_bytes(v, cache_lds, slide && a.span_stash != 0);

@@ -122,6 +122,34 @@ def test_word_span_variants_single_worker_match_oracle(w2v, arch, dim, k, stash)
     assert row_rel_err(g1[:s.voc.V - 1], a1) <= 1e-4
 
 
+# The sixteen-wavefront variants run where the wavefronts fill the chip. One document of at most 128 tokens is one
+# work unit, so one of 4,096 wavefronts trains it and the result is the sequential one (write-backs that add the
+# change: the other workgroups have none).
+@pytest.mark.parametrize("arch,dim,win,wp,k,stash", [
+    (0, 65, 5, 5, 31, 0), (0, 100, 2, 7, 31, 0), (0, 128, 4, 7, 0, 0), (0, 129, 5, 15, 31, 0), (0, 256, 5, 15, 31, 1),
+    (0, 200, 3, 15, 64, 0), (1, 129, 5, 15, 31, 0), (1, 256, 2, 15, 31, 1), (1, 200, 5, 15, 31, 0),
+])
+def test_sixteen_wavefronts_single_unit_matches_oracle(w2v, arch, dim, win, wp, k, stash):
+    log(f"sixteen wavefronts arch={arch} dim={dim} window={win} write_policy={wp} k={k} stash={stash}")
+    s = oracle_side("tiny_sg_v1k_d50")
+    voc = w2v.build_vocab(to_dev(s.tok), s.w.vocab, s.w.min_count)
+    tree = w2v.build_huffman(voc.vocab_counts)
+    tv = s.tv[:128]
+    syn0, syn1 = synth.init_weights(s.voc.V, dim, syn1_scale=0.5 / dim)
+    a0, a1 = syn0.copy(), syn1.copy()
+    op = oracle.params(s.voc.V, dim, window=win, sample=0.0, train_words=s.voc.train_words, arch=arch,
+                       corpus_tokens=s.tv.size, cache_k=k, flush_every=10, order=1, doc_len=128)
+    ost = oracle.train(a0, a1, s.tree, tv, op)
+    model = w2v.make_model(syn0, syn1, voc, tree)
+    p = w2v.Params(window=win, sample=0.0, corpus_tokens=s.tv.size, cache_k=k, flush_every=10, flush_policy=0,
+                   workers=4096, arch=arch, write_policy=wp, doc_len=128, span_stash=stash, stash_from=0)
+    st = w2v.train_hs_epoch(model, to_dev(tv), p).cpu().numpy()
+    assert list(st) == list(ost)
+    g0, g1 = (t.cpu().numpy() for t in model.vectors())
+    assert row_rel_err(g0, a0) <= 1e-4
+    assert row_rel_err(g1[:s.voc.V - 1], a1) <= 1e-4
+
+
 # ------------------------------------------------------------- synchronous mode
 # Every variant (rows of up to 64, 128, 256, 320, 512 and 1024 floats) at both ends of its range, windows that
 # take one group of words and several (12, 8 or 4 words a group), single-word windows, batches of one and of
