@@ -18,6 +18,7 @@
 
 #include "w2v_internal.h"
 #include "w2v_scan.h"
+#include "w2v_tiles.h"
 
 namespace w2v {
 
@@ -394,14 +395,12 @@ struct LogSigmoidSum {
 // rows a load, in the form that mfma4 multiplies. The first FULL tiles lie within the row.
 template <int FULL, int NE>
 __device__ __forceinline__ void load_quad_rows(f4 (&r)[NE], const float *m, int stride, int dim, int c0, int row, int lane) {
-    const float *p = m + static_cast<int64_t>(row) * stride + c0 + (lane >> 2) * 4;
+    const float *p = m + static_cast<int64_t>(row) * stride;
 #pragma unroll
     for (int t = 0; t < NE; ++t) {
-        if (t < FULL) {
-            r[t] = *reinterpret_cast<const f4 *>(p + t * kWave);
-        } else {
+        r[t] = *reinterpret_cast<const f4 *>(p + quad_column(FULL, c0, t, lane, dim));
+        if (t >= FULL) {
             const int col = c0 + t * kWave + (lane >> 2) * 4;
-            r[t] = *reinterpret_cast<const f4 *>(p + (col < dim ? t * kWave : -c0));
 #pragma unroll
             for (int i = 0; i < 4; ++i) r[t][i] = col + i < dim ? r[t][i] : 0.0f;
         }
@@ -677,15 +676,18 @@ __global__ __launch_bounds__(kSumThreads) void k_sum_stretches(const double *__r
 }
 
 using LLFn = void (*)(LLArgs);
-// 4 G window words per step: all of a window of half-width 5 for rows of up to 128 floats, eight words above.
+// 4 groups of window words per step: all of a window of half-width 5 for rows of up to 128 floats, eight words above.
+template <int I>
+constexpr LLFn ll_variant() {
+    constexpr LoglikTiles t = kLoglikTiles[I];
+    return k_loglik<t.tiles, t.groups, t.full, t.panels>;
+}
 LLFn pick_ll(int dim) {
-    const int ne = (dim + kWave - 1) / kWave;
-    if (ne <= 1) return k_loglik<1, 3, 0>;
-    if (ne <= 2) return k_loglik<2, 3, 1>;
-    if (ne <= 4) return k_loglik<4, 2, 2>;
-    if (ne <= 5) return k_loglik<5, 2, 4>;
-    if (ne <= 8) return k_loglik<8, 2, 5>;
-    return k_loglik<8, 2, 0, true>;
+    constexpr LLFn fns[] = {ll_variant<0>(), ll_variant<1>(), ll_variant<2>(),
+                            ll_variant<3>(), ll_variant<4>(), ll_variant<5>()};
+    int i = 0;
+    while (dim > kLoglikTiles[i].columns) ++i;   // dim <= 1024
+    return fns[i];
 }
 
 LLFn pick_ll_cbow(int dim) {
