@@ -150,11 +150,7 @@ typedef struct {
                                 512 floats with window <= 5: CBOW always, skip-gram on the store-only walk
                                 (bit 0; bit 2 when cache_k > 0; hot_k 0; cache_mode 0) and with window <= 2
                                 above 320 floats; elsewhere the bit is ignored; w2v_train_word_span reports
-                                which. Skip-gram rows of up to 128 floats with window <= 5, on the store-only walk (bit 0;
-                                bit 2 when cache_k > 0; hot_k 0; cache_mode 0) and a cache that fits beside 4 KiB
-                                of records per wavefront: bit 1 makes no difference; every centre reads its window
-                                rows, and what a wavefront changes in one is added atomically when that position
-                                leaves the window */
+                                which */
     int32_t flush_policy;    /* cache write-back: 0 = add the change (cached - original), the write-back of
                                 §3.2 as printed (stable at a few hundred wavefronts; at full occupancy the
                                 top rows' summed stale changes diverge); 1 = add the change divided by the

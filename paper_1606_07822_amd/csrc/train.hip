@@ -959,242 +959,6 @@ __global__ __launch_bounds__(WPB *kWave) void k_train(TrainArgs a) {
     }
 }
 
-// Skip-gram with the word rows' changes kept across centres (narrow rows, windows of at most H = PG/2, the
-// store-only walk). Every centre reads its window rows afresh, but what a wavefront adds to a word row stays
-// in its registers (e) while that position is within H of the centre and goes to memory as one atomic add
-// when it leaves, instead of one write per centre and pair; the rows a centre trains on are the ones read
-// plus the wavefront's own pending changes. One wavefront therefore computes what it would with a write per
-// centre, no update is lost, and the next centre's rows can be read while this one is trained.
-// What bounded narrow rows was the write of every window row at every centre (at 1e7 tokens, V = 30K, d = 100
-// the epoch took 24.9 ms without its arithmetic, 10.8 without its word-row writes) and then the walk's serial
-// arithmetic: 43.4 ms with an atomic add per pair (write_policy 5), 26.0 with a store per pair (7), 20.8 here
-// for both; 5.7 -> 4.5 ms at 1e5 tokens, V = 1K, d = 50. Sixteen wavefronts a workgroup (the ten slots leave
-// 113 VGPRs) against twelve: 20.8 against 24.0 ms.
-//
-// Slots as in the span (q < H: position j-H+q, q >= H: j+1+q-H), and one more, PG, for the centre's own word
-// (its pending change from the centres before it). Slots of one word each keep their own change; a window
-// row gets all of them, and a slot that leaves hands its change to another slot of its word if there is one
-// (the next centre's rows may have been read already), else to memory.
-template <int NE, int PG, int WPB>
-__global__ __launch_bounds__(WPB *kWave) void k_train_defer(TrainArgs a) {
-    constexpr int H = PG / 2;
-    const int LS = lds_stride<NE>(a.dim);
-    extern __shared__ float lds[];
-    float *val = lds;
-    float *orig = lds + a.cache_k * LS;
-    __shared__ unsigned s_centres;   // centres of the workgroup since its last write-back, modulo flush_every
-    __shared__ int s_lock;
-    __shared__ int4 s_rec[WPB][kSegLen];    // vocabulary index, meta, path offset, path length
-    __shared__ int4 s_rec2[WPB][kSegLen];   // code, learning rate
-    __shared__ int s_word[WPB][kSegLen + PG + 1];   // the kept words at positions j0 - H .. j1 + H, -1 past the document
-    const int lane = lane_id();
-    const int wib = static_cast<int>(threadIdx.x / kWave);
-    if (threadIdx.x == 0) {
-        s_centres = 0;
-        s_lock = 0;
-    }
-    const int kd = a.cache_k * LS;
-    for (int i = threadIdx.x; i < kd; i += blockDim.x) {
-        const int s = i / LS, col = i - s * LS;
-        const float v = col < a.dim ? a.syn1[static_cast<int64_t>(a.cache_first + s) * a.stride + col] : 0.0f;
-        val[i] = v;
-        orig[i] = v;
-    }
-    __syncthreads();
-
-    const int gw = blockIdx.x * WPB + wib;
-    uint64_t n_kept = 0, n_pairs = 0, n_nodes = 0;
-    const int4 *rec = s_rec[wib], *rec2 = s_rec2[wib];
-    // slot's place in s_word relative to the centre's (slot PG: the centre itself)
-    const int at = lane < H ? lane : (lane < PG ? lane + 1 : H);
-    while (gw < a.workers) {
-        int unit = 0;
-        if (lane == 0) unit = atomicAdd(a.queue, 1);
-        unit = __builtin_amdgcn_readfirstlane(unit);
-        if (unit >= a.n_units) break;
-        const int doc = unit / a.segs_per_doc;
-        const int nk = a.doc_kept[doc];
-        const int j0 = (unit - doc * a.segs_per_doc) * a.seg_len;
-        if (j0 >= nk) continue;
-        const int nc = min(nk, j0 + a.seg_len) - j0;   // centres of the segment
-        const int64_t base = static_cast<int64_t>(doc) * a.doc_len;
-        const int32_t *kv = a.kept_vid + base;
-        const uint32_t *km = a.kept_meta + base;
-        for (int q = lane; q < nc; q += kWave) {
-            const int v = kv[j0 + q];
-            const uint32_t meta = km[j0 + q];
-            const int64_t g = a.epoch_base + a.first_raw + base + static_cast<int64_t>(meta & 0xFFFFu);
-            const uint64_t code = a.code[v];
-            s_rec[wib][q] = make_int4(v, static_cast<int>(meta), a.point_off[v], static_cast<int>(a.codelen[v]));
-            s_rec2[wib][q] = make_int4(static_cast<int>(code), static_cast<int>(code >> 32),
-                                       __builtin_bit_cast(int, a.alpha_tab[g / 10000 - a.blk0]), 0);
-        }
-        for (int q = lane; q < nc + PG; q += kWave) {
-            const int pos = j0 - H + q;
-            s_word[wib][q] = pos >= 0 && pos < nk ? kv[pos] : -1;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-        // the path of centre q (lane l: its l-th node; empty ranges past its end)
-        auto fetch_path = [&](int q) {
-            const int po = __builtin_amdgcn_readfirstlane(rec[q].z), len = __builtin_amdgcn_readfirstlane(rec[q].w);
-            const auto pr = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(a.points) + po, 0, len * 4,
-                                                              kRawBufferWord3);
-            return static_cast<int>(__builtin_amdgcn_raw_buffer_load_b32(pr, lane_bytes(lane), 0, 0));
-        };
-        auto window_slots = [&](int q, int &p0, int &p1) {
-            const int j = j0 + q;
-            const int eff = static_cast<int>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(rec[q].y)) >> 16);
-            p0 = H - min(eff, j);
-            p1 = H + min(eff, nk - 1 - j);
-        };
-        // the rows of the window words (zeros in the other slots)
-        auto load_window = [&](float(&x)[PG][NE], int sid, int p0, int p1) {
-#pragma unroll
-            for (int q = 0; q < PG; ++q) {
-                const int w = __builtin_amdgcn_readlane(sid, q);
-                const bool in = q >= p0 && q < p1;
-                buf_load_row<NE>(x[q], row_rsrc(a.syn0, in ? w : 0, a.stride, in ? a.dim * 4 : 0), lane);
-            }
-        };
-        float e[PG + 1][NE], xn[PG][NE];
-#pragma unroll
-        for (int q = 0; q <= PG; ++q) zero_row<NE>(e[q]);
-        uint32_t dirty = 0;
-        int sid = lane <= PG ? s_word[wib][at] : -1;
-        int pairs = span_pairs<PG + 2>(sid, lane);   // pairs of slots 0 .. PG that hold the same word
-        int p0, p1;
-        window_slots(0, p0, p1);
-        int pt_next = fetch_path(0);
-        load_window(xn, sid, p0, p1);
-        for (int q = 0; q < nc; ++q) {
-            const int4 r2 = rec2[q];
-            const int len = __builtin_amdgcn_readfirstlane(rec[q].w);
-            int my_pt = pt_next;
-            asm volatile("" : "+v"(my_pt));
-            float x[PG][NE];
-#pragma unroll
-            for (int s = 0; s < PG; ++s)
-#pragma unroll
-                for (int i = 0; i < NE; ++i) x[s][i] = xn[s][i] + e[s][i];
-            if (pairs > 0) {   // the pending changes of the other slots of a window word
-#pragma unroll
-                for (int s = 0; s < PG; ++s) {
-                    if (s >= p0 && s < p1) {
-                        const int w = __builtin_amdgcn_readlane(sid, s);
-                        const uint64_t m = __ballot(lane <= PG && lane != s && sid == w);
-#pragma unroll
-                        for (int t = 0; t <= PG; ++t)
-                            if ((m >> t) & 1ull)
-#pragma unroll
-                                for (int i = 0; i < NE; ++i) x[s][i] += e[t][i];
-                    }
-                }
-            }
-            // the next centre's path and window rows, read while this one is trained
-            const int qn = min(q + 1, nc - 1);
-            const int sidn = lane <= PG ? s_word[wib][qn + at] : -1;
-            int p0n, p1n;
-            window_slots(qn, p0n, p1n);
-            pt_next = fetch_path(qn);
-            load_window(xn, sidn, p0n, p1n);
-
-            const int P = p1 - p0;
-            ++n_kept;
-            if (P > 0) {
-                const uint64_t code = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(r2.x)) |
-                                      static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(r2.y))) << 32;
-                const float alpha = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(r2.z));
-                float(&ew)[PG][NE] = *reinterpret_cast<float(*)[PG][NE]>(&e[0]);
-                walk_path<NE, PG, kPfBuf>(a, val, x, ew, p0, p1, my_pt, len, code, alpha, lane);
-                dirty |= ((1u << p1) - 1u) & ~((1u << p0) - 1u);
-                n_pairs += P;
-                n_nodes += static_cast<uint64_t>(P) * len;
-            }
-            if (a.cache_k > 0) {
-                int go = 0;
-                if (lane == 0) {
-                    const unsigned c = atomicInc(&s_centres, static_cast<unsigned>(a.flush_every - 1));
-                    if (c == static_cast<unsigned>(a.flush_every - 1)) go = (atomicCAS(&s_lock, 0, 1) == 0) ? 1 : 0;
-                }
-                go = __builtin_amdgcn_readfirstlane(go);
-                if (go) {
-                    flush_cache_wave<4>(a, false, val, orig, LS, lane);
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                    if (lane == 0) atomicExch(&s_lock, 0);
-                }
-            }
-            if (q + 1 == nc) break;
-            // to the next centre: slot 0 leaves, slot H becomes the centre's, the centre's becomes slot H-1
-            const int w0 = __builtin_amdgcn_readlane(sid, 0), wn = __builtin_amdgcn_readlane(sidn, PG - 1);
-            float left[NE];
-#pragma unroll
-            for (int i = 0; i < NE; ++i) left[i] = e[0][i];
-            const uint64_t heirs = w0 >= 0 ? __ballot(lane <= PG && sidn == w0) : 0ull;
-            const uint64_t twins = w0 >= 0 ? __ballot(lane > 0 && lane <= PG && sid == w0) : 0ull;
-            const uint64_t joins = wn >= 0 ? __ballot(lane <= PG && lane != PG - 1 && sidn == wn) : 0ull;
-            pairs += __popcll(joins) - __popcll(twins);
-            const bool left_dirty = (dirty & 1u) != 0;
-            if (left_dirty && heirs == 0ull)
-                atomic_add_row<NE>(a.syn0 + static_cast<int64_t>(w0) * a.stride, left, lane, a.dim, a.full_rows);
-            float next_c[NE];
-#pragma unroll
-            for (int i = 0; i < NE; ++i) next_c[i] = e[H][i];
-            const uint32_t low = (1u << (H - 1)) - 1u;
-            const uint32_t next_dirty = ((dirty >> 1) & low) | ((dirty >> PG & 1u) << (H - 1)) |
-                                        (((dirty >> (H + 1)) & low) << H) | ((dirty >> H & 1u) << PG);
-#pragma unroll
-            for (int s = 0; s + 1 < H; ++s)
-#pragma unroll
-                for (int i = 0; i < NE; ++i) e[s][i] = e[s + 1][i];
-#pragma unroll
-            for (int i = 0; i < NE; ++i) e[H - 1][i] = e[PG][i];
-#pragma unroll
-            for (int s = H; s + 1 < PG; ++s)
-#pragma unroll
-                for (int i = 0; i < NE; ++i) e[s][i] = e[s + 1][i];
-            zero_row<NE>(e[PG - 1]);
-#pragma unroll
-            for (int i = 0; i < NE; ++i) e[PG][i] = next_c[i];
-            dirty = next_dirty;
-            if (left_dirty && heirs != 0ull) {
-                const uint64_t first = heirs & (~heirs + 1ull);
-#pragma unroll
-                for (int t = 0; t <= PG; ++t) {
-                    if (first == (1ull << t)) {
-#pragma unroll
-                        for (int i = 0; i < NE; ++i) e[t][i] += left[i];
-                        dirty |= 1u << t;
-                    }
-                }
-            }
-            sid = sidn;
-            p0 = p0n;
-            p1 = p1n;
-        }
-#pragma unroll
-        for (int s = 0; s <= PG; ++s) {
-            if ((dirty >> s) & 1u) {
-                const int w = __builtin_amdgcn_readlane(sid, s);
-                atomic_add_row<NE>(a.syn0 + static_cast<int64_t>(w) * a.stride, e[s], lane, a.dim, a.full_rows);
-            }
-        }
-    }
-    if (lane == 0 && n_kept) {
-        atomicAdd(&a.stats[0], static_cast<unsigned long long>(n_kept));
-        atomicAdd(&a.stats[1], static_cast<unsigned long long>(n_pairs));
-        atomicAdd(&a.stats[2], static_cast<unsigned long long>(n_nodes));
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < kd; i += blockDim.x) {   // final write-back of the cache
-        const float d = (val[i] - orig[i]) * a.flush_scale;
-        const int s = i / LS, col = i - s * LS;
-        if (d != 0.0f && col < a.dim) atomicAdd(a.syn1 + static_cast<int64_t>(a.cache_first + s) * a.stride + col, d);
-    }
-}
-
 struct Variant {
     void (*fn)(TrainArgs);
     int waves_per_block;
@@ -1231,33 +995,14 @@ Variant pick_variant(int arch, int dim, bool buf, bool slide = false) {
     return variant<16, 2, 8, kPfSuffix>(arch, false);
 }
 
-// Word-row changes kept across centres (k_train_defer): skip-gram on the store-only walk, rows of up to 128
-// floats, windows of up to 5, where the larger centre records leave room for the cache; elsewhere each
-// centre writes its window rows.
-template <int NE, int PG, int WPB>
-constexpr Variant defer_variant() {
-    constexpr int rb = WPB * (2 * kSegLen * static_cast<int>(sizeof(int4)) +
-                              (kSegLen + PG + 1) * static_cast<int>(sizeof(int)));
-    return Variant{k_train_defer<NE, PG, WPB>, WPB, NE, PG, lds_stride<NE>, rb};
-}
-
 // Sixteen wavefronts a workgroup instead of twelve pay where the text (or the caller's number of workers) gives
 // nearly every compute unit such a workgroup. A shorter text has fewer wavefronts than fit (kMinUnitsPerWave work
 // units each): sixteen to a workgroup then crowd them onto fewer compute units. 2e6 tokens, V = 100K, 1e-3
-// subsampling: d = 200 10.3 ms with twelve, 12.0 with sixteen (CBOW 6.5, 7.3), d = 100 (policy 7) 8.6 with twelve
-// (9.0 with a write per centre), 9.7 with sixteen. 4e6 tokens, 97 % of the compute units: d = 200 13.2 with
-// twelve, 12.4 with sixteen (8.4, 7.5).
+// subsampling, d = 200: 10.3 ms with twelve, 12.0 with sixteen (CBOW 6.5, 7.3). 4e6 tokens, 97 % of the compute
+// units: 13.2 with twelve, 12.4 with sixteen (8.4, 7.5).
 bool fills_chip(int waves_per_block, int workers, int64_t n_units) {
     const int64_t waves = workers > 0 ? workers : n_units / kMinUnitsPerWave;
     return waves * 16 >= static_cast<int64_t>(waves_per_block) * device_cu_count() * 15;
-}
-
-bool defer_variant_for(int arch, int dim, bool buf, int window, size_t cache_k, bool fills, Variant *v) {
-    if (arch != 0 || !buf || dim > 2 * kWave || window > 5) return false;
-    if (dim <= kWave) *v = window <= 2 ? defer_variant<1, 4, 16>() : defer_variant<1, 10, 16>();
-    else if (fills) *v = window <= 2 ? defer_variant<2, 4, 16>() : defer_variant<2, 10, 16>();
-    else *v = window <= 2 ? defer_variant<2, 4, 12>() : defer_variant<2, 10, 12>();
-    return 2 * cache_k * v->ls(dim) * sizeof(float) + static_cast<size_t>(v->rec_bytes) + 1024 <= device_max_lds();
 }
 
 // Word-row span at 129 to 256 columns: sixteen wavefronts a workgroup where the text fills the chip with them and
@@ -1327,7 +1072,7 @@ int launch_shape(const Variant &v, size_t lds, int workers, int64_t n_units, int
 
 }  // namespace
 
-// Launch shape of the walk that keeps no word rows or changes across centres (the one that may park gradients).
+// Launch shape of the walk that keeps no word rows across centres (the one that may park gradients).
 int train_launch_shape(int arch, int dim, int cache_k, bool delta, bool buf, int workers, int64_t n_units, int *grid,
                        int *waves) {
     const Variant v = pick_variant(arch, dim, buf);
@@ -1358,9 +1103,8 @@ int launch_train_async(TrainArgs a, int arch, int window, hipEvent_t ev0, hipEve
     const bool slide = train_slide(arch, a.dim, a.stores_only != 0, a.write_policy, window);
     Variant v;
     const size_t wide_cache = (a.cache_delta ? 1ull : 2ull) * a.cache_k * lds_stride<4>(a.dim) * sizeof(float);
-    const bool fills = fills_chip(16, a.workers, a.n_units);
-    if (slide ? !(fills && wide_span_variant(arch, a.dim, a.stores_only != 0, a.span_stash != 0, wide_cache, &v))
-              : !defer_variant_for(arch, a.dim, a.stores_only != 0, window, static_cast<size_t>(a.cache_k), fills, &v))
+    if (!(slide && fills_chip(16, a.workers, a.n_units) &&
+          wide_span_variant(arch, a.dim, a.stores_only != 0, a.span_stash != 0, wide_cache, &v)))
         v = pick_variant(arch, a.dim, a.stores_only != 0, slide);
     const size_t cache_lds = (a.cache_delta ? 1ull : 2ull) * a.cache_k * v.ls(a.dim) * sizeof(float);
     const size_t stash = span_stash_bytes(v, cache_lds, slide && a.span_stash != 0);

@@ -60,12 +60,11 @@ def test_huffman_too_deep_at_any_generation_is_an_error(w2v, V):
     assert e.value.code == w2v.W2V_E_RANGE
 
 
-# ------------------------------------------------------------- word-row changes kept across centres
-# Skip-gram rows of up to 128 floats with windows of up to 5 keep a word row's change in the wavefront until its
-# position leaves the window: the widest and narrowest row of each variant, windows of both, every write policy
-# that takes it, no subsampling over 1,000 words (repeated words in most windows), short documents, and the
-# settings that fall back (a cache too large for the centre records, windows above 5). The bar is the one of the
-# other single-worker tests: sums in another order and the fast sigmoid, carried through the updates.
+# ------------------------------------------------------------- narrow rows
+# Skip-gram rows of up to 128 floats on the store-only walk: the widest and narrowest row of each variant, every
+# write policy that takes it, no subsampling over 1,000 words (repeated words in most windows), short documents, a
+# large cache, windows above 5. The bar is the one of the other single-worker tests: sums in another order and the
+# fast sigmoid, carried through the updates.
 @pytest.mark.parametrize("name,sample,dim,win,wp,k,doc_len", [
     ("tiny_sg_v1k_d50", 0.0, 50, 2, 5, 31, 1000), ("tiny_sg_v1k_d50", 0.0, 64, 5, 7, 31, 1000),
     ("tiny_sg_v1k_d50", 0.0, 65, 5, 5, 31, 1000), ("tiny_sg_v1k_d50", 0.0, 1, 3, 15, 7, 1000),
@@ -96,6 +95,38 @@ def test_narrow_rows_single_worker_matches_oracle(w2v, name, sample, dim, win, w
     assert row_rel_err(g1[:s.voc.V - 1], a1) <= 1e-4
 
 
+# Text without subsampling at full occupancy: thousands of wavefronts train the most frequent words at once, and what
+# each adds to their rows was computed without the others' latest. The longer a wavefront holds a change back, the
+# lower the learning rate at which the sums overshoot: with a change kept until its position leaves the window these
+# rates diverge (at window 5 from 0.016 on), with a write per centre they are two thirds of the limit (0.038 and
+# 0.048), and stored rows (write_policy 7) have none. The untrained model's log-likelihood is beaten by 0.3 or more.
+@pytest.mark.parametrize("V,dim,win,wp,alpha", [(50, 50, 5, 5, 0.025), (300, 100, 3, 5, 0.03), (1000, 100, 5, 7, 0.05),
+                                                (50, 50, 5, 7, 0.05)])
+def test_unsubsampled_text_trains_at_full_occupancy(w2v, V, dim, win, wp, alpha):
+    log(f"unsubsampled V={V} dim={dim} window={win} write_policy={wp} alpha={alpha}")
+    n, g = 4_000_000, torch.Generator(device="cuda").manual_seed(3)
+    prob = 1.0 / torch.arange(1, V + 1, device="cuda", dtype=torch.float64)
+    prob /= prob.sum()
+    tok = torch.searchsorted(torch.cumsum(prob, 0), torch.rand(n, generator=g, device="cuda", dtype=torch.float64))
+    # a document's topic, one word of each 20 neighbouring ranks, takes half of its tokens
+    topic = torch.randint(20, (n // 1000,), generator=g, device="cuda").repeat_interleave(1000)
+    tok = torch.where(torch.rand(n, generator=g, device="cuda") < 0.5, tok // 20 * 20 + topic, tok).clamp_(max=V - 1).int()
+    voc = w2v.Vocab(None, None, (prob * n).long() + 5, None, V, int(((prob * n).long() + 5).sum()), None)
+    syn0, syn1 = synth.init_weights(V, dim)
+    model = w2v.make_model(syn0, syn1, voc, w2v.build_huffman(voc.vocab_counts))
+
+    def ll():
+        s, pairs, _ = w2v.hs_loglik(model, tok[:200_000], w2v.Params(window=win, seed=4))
+        return s / pairs
+
+    before = ll()
+    w2v.train_hs_epoch(model, tok, w2v.Params(window=win, alpha0=alpha, write_policy=wp))
+    after = ll()
+    log(f"  untrained {before:.4f} trained {after:.4f} largest {float(model.syn0.abs().max()):.2f}")
+    assert all(bool(torch.isfinite(t).all()) for t in model.vectors())
+    assert after > before + 0.2
+
+
 # Word rows kept across centres at 129 to 256 floats: the sixteen-wavefront variant, and the twelve-wavefront one
 # where the cache (or the cache and the stash) leaves no room for it.
 @pytest.mark.parametrize("arch", [0, 1])
@@ -122,9 +153,10 @@ def test_word_span_variants_single_worker_match_oracle(w2v, arch, dim, k, stash)
     assert row_rel_err(g1[:s.voc.V - 1], a1) <= 1e-4
 
 
-# The sixteen-wavefront variants run where the wavefronts fill the chip. One document of at most 128 tokens is one
-# work unit, so one of 4,096 wavefronts trains it and the result is the sequential one (write-backs that add the
-# change: the other workgroups have none).
+# The sixteen-wavefront variants (129 to 256 floats) run where the wavefronts fill the chip; up to 128 floats the
+# same launch runs the variants that short texts take. One document of at most 128 tokens is one work unit, so one of
+# 4,096 wavefronts trains it and the result is the sequential one (write-backs that add the change: the other
+# workgroups have none).
 @pytest.mark.parametrize("arch,dim,win,wp,k,stash", [
     (0, 65, 5, 5, 31, 0), (0, 100, 2, 7, 31, 0), (0, 128, 4, 7, 0, 0), (0, 129, 5, 15, 31, 0), (0, 256, 5, 15, 31, 1),
     (0, 200, 3, 15, 64, 0), (1, 129, 5, 15, 31, 0), (1, 256, 2, 15, 31, 1), (1, 200, 5, 15, 31, 0),
