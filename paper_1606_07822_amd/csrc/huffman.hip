@@ -43,8 +43,14 @@ constexpr int kChunk = 2 * kMergeThreads;   // elements of S per chunk: one merg
 constexpr int kMaxMergeGroups = 128;
 constexpr int kMaxGenerations = 72;
 
-__global__ void k_check_descending(const int64_t *__restrict__ counts, int32_t V, int32_t *__restrict__ flags) {
+// Entry of `up` that no merge has written. Counts whose sums pass 2^63 give queues that are not ascending, and
+// the merge then takes some nodes twice and others never; k_huff_codes refuses a path through one of those.
+constexpr uint32_t kNoParent = ~0u;
+
+__global__ void k_check_descending(const int64_t *__restrict__ counts, int32_t V, uint2 *__restrict__ up,
+                                   int32_t *__restrict__ flags) {
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < V) up[i] = make_uint2(kNoParent, kNoParent);   // two of the 2 V entries
     if (i + 1 < V && counts[i] < counts[i + 1]) atomicOr(&flags[2], 1);
 }
 
@@ -156,8 +162,8 @@ __global__ __launch_bounds__(kMergeThreads) void k_huff_merge(const int64_t *__r
             }
             const bool ends = k0 + kChunk >= 2LL * M;   // S's last chunk: all leaves come before its end
             const int32_t n = static_cast<int32_t>(ends ? 2LL * M - k0 : kChunk);
-            // (the clamps only matter for counts whose sums are not ascending -- negative ones, or past 63 bits:
-            // a search then ends anywhere in its range, and every index still stays within its queue)
+            // (the clamps only matter for counts whose sums pass 63 bits and are not ascending: a search then ends
+            // anywhere in its range, and every index still stays within its queue)
             const int32_t i0 = s_i0, i1 = max(i0, min(ends ? nl : s_i1, min(i0 + n, left)));
             const int32_t j0 = static_cast<int32_t>(k0) - i0;
             const int32_t lw = i1 - i0, iw = n - lw;
@@ -196,7 +202,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_huff_merge(const int64_t *__r
     }
 }
 
-// codelen / code per leaf; error flag (code longer than 64). Depth does not fall along the queues (the inner
+// codelen / code per leaf; error flag (code longer than 64, or a node that was never merged). Depth does not fall along the queues (the inner
 // queue is first in, first out, so an earlier node's parent is never later), so the last word has the longest
 // code.
 __global__ void k_huff_codes(const uint32_t *__restrict__ up, int32_t V, uint8_t *__restrict__ codelen,
@@ -213,7 +219,7 @@ __global__ void k_huff_codes(const uint32_t *__restrict__ up, int32_t V, uint8_t
     uint64_t rev = 0;
     while (node != root) {
         const uint32_t u = up[node];
-        if (depth >= 64) {
+        if (depth >= 64 || u >> 1 > static_cast<uint32_t>(V - 2)) {
             atomicOr(&flags[3], 1);
             codelen[v] = 0;
             code[v] = 0;
@@ -355,7 +361,7 @@ int run_build_huffman(const int64_t *vocab_counts, int32_t V, uint8_t *codelen, 
     uint32_t *arrived = reinterpret_cast<uint32_t *>(flags + 4);
     const unsigned gv = static_cast<unsigned>(ceil_div(V, 256));
     k_zero_i32<<<1, 64, 0, s>>>(flags, 8);
-    k_check_descending<<<gv, 256, 0, s>>>(vocab_counts, V, flags);
+    k_check_descending<<<gv, 256, 0, s>>>(vocab_counts, V, reinterpret_cast<uint2 *>(up), flags);
     W2V_LAUNCH_CHECK("k_check_descending");
     // a workgroup per chunk of the largest possible generation (all leaves and half as many nodes), at most one
     // per two compute units

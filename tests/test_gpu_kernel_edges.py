@@ -60,6 +60,20 @@ def test_huffman_too_deep_at_any_generation_is_an_error(w2v, V):
     assert e.value.code == w2v.W2V_E_RANGE
 
 
+# Counts (runs of multiples of 2^60) whose sums pass 2^63: the merge's queues are no longer ascending, some inner
+# nodes are never taken, and the paths of the words below them (a model of the merge on the CPU: 4 to 9 of them,
+# whichever of two writers of another entry wins) end there. They are refused, and nothing is read through them.
+@pytest.mark.parametrize("runs", [
+    [(7, 6), (6, 7), (5, 4), (4, 3), (3, 4), (2, 2), (1, 5)], [(7, 3), (6, 1), (5, 4), (4, 7), (3, 8), (2, 4), (1, 5)],
+    [(7, 4), (6, 7), (5, 6), (4, 3), (3, 4), (2, 6), (1, 3)],
+])
+def test_huffman_counts_past_63_bits_are_an_error(w2v, runs):
+    counts = np.concatenate([np.full(n, x << 60, np.int64) for x, n in runs])
+    with pytest.raises(w2v.W2VError) as e:
+        w2v.build_huffman(to_dev(counts))
+    assert e.value.code == w2v.W2V_E_RANGE
+
+
 # ------------------------------------------------------------- narrow rows
 # Skip-gram rows of up to 128 floats on the store-only walk: the widest and narrowest row of each variant, every
 # write policy that takes it, no subsampling over 1,000 words (repeated words in most windows), short documents, a
