@@ -41,7 +41,7 @@ struct SyncArgs {
     int64_t first_raw, epoch_base;
     const float *alpha_tab;
     int64_t blk0;
-    int64_t c_lo, c_hi;        // global kept indices of this batch
+    int64_t c_lo;              // global kept index of this launch's first centre
     unsigned long long *d0;    // [V][dim] fixed-point deltas of syn0
     unsigned long long *d1;    // [V-1][dim] of syn1
     int32_t *flag0, *flag1;    // touched rows
@@ -69,6 +69,7 @@ __device__ __forceinline__ void touch(int32_t *flag, int32_t *list, int32_t *cnt
 // this takes about 17 (an epoch of 305 such batches 7.6 instead of 64.8 ms; with four wavefronts 8.4, and with
 // the words' sums added by each of four or eight wavefronts 10.4 and 15.0).
 constexpr int kSyncWaves = 8;
+constexpr int64_t kSyncCentres = int64_t(1) << 22;   // centres a launch: HIP takes fewer than 2^32 threads (2^23 centres)
 template <int NE, int GW>
 __global__ __launch_bounds__(kSyncWaves *kWave) void k_sync_grad(SyncArgs a) {
     __shared__ unsigned long long s_dx[GW][NE * kWave];   // the group's words' changes over all nodes
@@ -294,10 +295,11 @@ int run_train_sync(const w2v_model *m, const w2v_params *p, const SampleBufs &b,
     const unsigned ag = static_cast<unsigned>(std::max(1, device_cu_count() * 4));
     int parity = 0;
     for (int64_t lo = 0; lo < kept; lo += p->sync_batch, parity ^= 1) {
-        a.c_lo = lo;
-        a.c_hi = std::min<int64_t>(kept, lo + p->sync_batch);
+        const int64_t hi = std::min<int64_t>(kept, lo + p->sync_batch);
         a.cnt = cnt + 2 * parity;
-        hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(a.c_hi - a.c_lo)), dim3(kSyncWaves * kWave), 0, s, a);
+        for (a.c_lo = lo; a.c_lo < hi; a.c_lo += kSyncCentres)
+            hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(std::min(hi - a.c_lo, kSyncCentres))),
+                               dim3(kSyncWaves * kWave), 0, s, a);
         k_sync_apply<<<ag, 256, 0, s>>>(a, m->syn0, m->syn1, cnt + 2 * (parity ^ 1));
         W2V_LAUNCH_CHECK("sync batch");
     }

@@ -225,6 +225,26 @@ def test_sync_variants_match_oracle(w2v, dim, win, batch):
     assert row_rel_err(g1[:s.voc.V - 1], a1) <= 1e-4
 
 
+# A batch of more centres than one launch's threads can number (2^32, 512 a centre): the sums of all of them are
+# taken against the model at the batch's start.
+def test_sync_batch_larger_than_a_launch_matches_oracle(w2v):
+    V, dim, n = 60, 4, (1 << 23) + 5
+    counts = np.sort(np.random.default_rng(1).integers(100, 10_000, V))[::-1].astype(np.int64)
+    tv = np.random.default_rng(2).integers(0, V, n).astype(np.int32)
+    voc = w2v.Vocab(None, None, to_dev(counts), None, V, int(counts.sum()), None)
+    syn0, syn1 = synth.init_weights(V, dim, syn1_scale=0.1)
+    a0, a1 = syn0.copy(), syn1.copy()
+    op = oracle.params(V, dim, window=1, sample=0.0, train_words=int(counts.sum()), corpus_tokens=n, sync_batch=1 << 30)
+    ost = oracle.train_sync(a0, a1, oracle.build_huffman(counts), tv, op, n_batches=-1)
+    model = w2v.make_model(syn0, syn1, voc, w2v.build_huffman(voc.vocab_counts))
+    p = w2v.Params(window=1, sample=0.0, corpus_tokens=n, mode=1, sync_batch=1 << 30, cache_k=0)
+    st = w2v.train_hs_epoch(model, to_dev(tv), p).cpu().numpy()
+    assert list(st) == list(ost) and st[2] == n
+    g0, g1 = (t.cpu().numpy() for t in model.vectors())
+    assert row_rel_err(g0, a0) <= 1e-4
+    assert row_rel_err(g1[:V - 1], a1) <= 1e-4
+
+
 # ------------------------------------------------------------- log-likelihood
 # Rows that end inside, at and just past a 64-column tile and a panel of 512 columns, rows that are not a
 # multiple of four floats (with NaN behind them), windows that take one and several groups of words, documents
