@@ -611,7 +611,7 @@ int run_ns_objective(const w2v_model *m, const int32_t *table, int32_t log2_size
     int64_t *out_t = c.take<int64_t>(1);
     if (a.n_docs > 0) {
         // one unit per wavefront: the hardware hands out workgroups as others finish
-        const unsigned grid = static_cast<unsigned>(std::min<int64_t>(ceil_div(a.obj_units, 4), INT32_MAX));
+        const unsigned grid = static_cast<unsigned>(std::min(ceil_div(a.obj_units, 4), kMaxGroups));
         NsFn fn = pick_ns(m->dim, p->negative, true);
         if (!fn) return fail(W2V_E_ARG, "no kernel variant for this dim and number of negatives");
         hipLaunchKernelGGL(fn, dim3(grid), dim3(256), 0, s, a);

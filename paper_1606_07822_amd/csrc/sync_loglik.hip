@@ -69,7 +69,6 @@ __device__ __forceinline__ void touch(int32_t *flag, int32_t *list, int32_t *cnt
 // this takes about 17 (an epoch of 305 such batches 7.6 instead of 64.8 ms; with four wavefronts 8.4, and with
 // the words' sums added by each of four or eight wavefronts 10.4 and 15.0).
 constexpr int kSyncWaves = 8;
-constexpr int64_t kSyncCentres = int64_t(1) << 22;   // centres a launch: HIP takes fewer than 2^32 threads (2^23 centres)
 template <int NE, int GW>
 __global__ __launch_bounds__(kSyncWaves *kWave) void k_sync_grad(SyncArgs a) {
     __shared__ unsigned long long s_dx[GW][NE * kWave];   // the group's words' changes over all nodes
@@ -297,8 +296,8 @@ int run_train_sync(const w2v_model *m, const w2v_params *p, const SampleBufs &b,
     for (int64_t lo = 0; lo < kept; lo += p->sync_batch, parity ^= 1) {
         const int64_t hi = std::min<int64_t>(kept, lo + p->sync_batch);
         a.cnt = cnt + 2 * parity;
-        for (a.c_lo = lo; a.c_lo < hi; a.c_lo += kSyncCentres)
-            hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(std::min(hi - a.c_lo, kSyncCentres))),
+        for (a.c_lo = lo; a.c_lo < hi; a.c_lo += kMaxGroups)
+            hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(std::min(hi - a.c_lo, kMaxGroups))),
                                dim3(kSyncWaves * kWave), 0, s, a);
         k_sync_apply<<<ag, 256, 0, s>>>(a, m->syn0, m->syn1, cnt + 2 * (parity ^ 1));
         W2V_LAUNCH_CHECK("sync batch");
@@ -745,7 +744,7 @@ int run_loglik(const w2v_model *m, const w2v_params *p, const SampleBufs &b, int
     if (a.n_units > 0) {
         // one unit per wavefront: the hardware hands out workgroups as others finish, which balances the
         // uneven units (a document's kept centres end in a partial unit, and units past them are empty)
-        const unsigned grid = static_cast<unsigned>(std::min<int64_t>(ceil_div(a.n_units, 4), INT32_MAX));
+        const unsigned grid = static_cast<unsigned>(std::min(ceil_div(a.n_units, 4), kMaxGroups));
         hipLaunchKernelGGL(cbow ? pick_ll_cbow(m->dim) : pick_ll(m->dim), dim3(grid), dim3(256), 0, s, a);
         W2V_LAUNCH_CHECK("k_loglik");
         int64_t *terms = cbow ? a.unit_terms : nullptr;

@@ -276,6 +276,11 @@ int launch_thresholds(const int64_t *vocab_counts, int32_t V, double sample, int
 // Learning-rate table: alpha of 10,000-token blocks [blk0, blk0 + nblk).
 int launch_alpha_table(const w2v_params *p, int64_t blk0, int64_t nblk, float *tab, hipStream_t s);
 
+// Workgroups (of up to 512 threads) of the launches that stride over their work: a launch numbers its threads in
+// 32 bits and covers only part of its grid past that, without an error (2^26 + 10 units of an objective ran on a
+// dozen wavefronts, for some 20 s).
+constexpr int64_t kMaxGroups = int64_t(1) << 22;
+
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Every inner-node row of the walk is written back by a store: uncached rows to HBM (write_policy bit 0)

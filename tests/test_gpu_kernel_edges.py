@@ -281,6 +281,30 @@ def test_loglik_variants_match_oracle(w2v, arch, dim, win, doc_len, deep):
     assert abs(s - so) <= (1e-12 if arch == 1 else 1e-6) * abs(so)
 
 
+# A text of more work units than one launch's wavefronts can number (2^26): its objective is the sum of its halves'.
+@pytest.mark.parametrize("kind", ["skip-gram", "cbow", "negative sampling"])
+def test_objective_of_more_units_than_a_launch_is_the_sum_of_its_halves(w2v, kind):
+    log(f"objective over 2^26 + 10 documents, {kind}")
+    V, dim, half = 50, 8, (1 << 26) + 10   # documents of two words: a work unit each
+    counts = to_dev(np.arange(V, 0, -1, dtype=np.int64) * 1000)
+    tok = torch.randint(V, (2 * half,), generator=torch.Generator(device="cuda").manual_seed(5), device="cuda",
+                        dtype=torch.int32)
+    voc = w2v.Vocab(None, None, counts, None, V, int(counts.sum()), None)
+    syn0, syn1 = synth.init_weights(V, dim, syn1_scale=0.5)
+    args = dict(window=1, doc_len=2, seed=4, arch=int(kind == "cbow"), negative=2)
+    if kind == "negative sampling":
+        model = w2v.make_ns_model(syn0, synth.init_weights(V, dim)[0], voc)
+        noise = w2v.build_noise_table(counts)
+        run = lambda t, first: w2v.ns_objective(model, noise, t, w2v.Params(first_raw_index=first, **args))
+    else:
+        model = w2v.make_model(syn0, syn1, voc, w2v.build_huffman(counts))
+        run = lambda t, first: w2v.hs_loglik(model, t, w2v.Params(first_raw_index=first, **args))
+    whole, a, b = run(tok, 0), run(tok[:half], 0), run(tok[half:], half)
+    assert whole[1:] == tuple(x + y for x, y in zip(a[1:], b[1:])) and whole[1] == 2 * half
+    # 64-bit sums of 2^27 terms of one sign, in another order
+    assert abs(whole[0] - (a[0] + b[0])) <= 1e-10 * abs(whole[0])
+
+
 # ------------------------------------------------------------- vocabulary
 # One tile of the sort and its edges, several, counts of one digit and of more, every id kept and every id dropped;
 # the long texts' lists (8 million tokens, ids past 36,864): ids that all go to the lists, which then overflow
