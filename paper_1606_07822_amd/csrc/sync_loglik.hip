@@ -536,13 +536,15 @@ __global__ __launch_bounds__(256, NE <= 5 ? 3 : 2) void k_loglik(LLArgs a) {
 }
 
 // CBOW: one wavefront per work unit; per centre with a window, h = (sum of the window rows in ascending window
-// order, fp64) / P, then one walk of the centre's path with fp64 dot products, four nodes at a time (the next
-// four rows loaded meanwhile) and reduced together; lane 16 r + k keeps node 4 k + r. Node after node, each with
-// a sum over the wavefront of its own, it took 2.11 ms for the 1e6-token held-out corpus at V = 100K, d = 300,
-// this 1.3 (four
-// wavefronts per SIMD; 1.7 with three).
+// order, fp64) / P, then one walk of the centre's path with fp64 dot products, four nodes at a time (up to 512 floats
+// the next four rows loaded meanwhile: wider ones have no registers for them) and reduced together; lane 16 r + k
+// keeps node 4 k + r. Node after node, each with a sum over the wavefront of its own, it took 2.11 ms for the
+// 1e6-token held-out corpus at V = 100K, d = 300, this 1.2 (four wavefronts per SIMD; 1.7 with three). Window words
+// four at a time pay for the words that a window does not have (1.3 ms; V = 100: 495 instead of 400 us for 3e5 tokens);
+// above 512 floats the next nodes' rows and two wavefronts per SIMD took 1.57 ms for 3e5 tokens at d = 600, this 0.79.
 template <int NE>
-__global__ __launch_bounds__(256, NE <= 5 ? 4 : (NE <= 8 ? 3 : 2)) void k_loglik_cbow(LLArgs a) {
+__global__ __launch_bounds__(256, NE <= 5 ? 4 : 3) void k_loglik_cbow(LLArgs a) {
+    constexpr bool kAhead = NE <= 8;
     const int lane = lane_id();
     const int64_t wave0 = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) / kWave;
     const int64_t nwaves = static_cast<int64_t>(gridDim.x) * blockDim.x / kWave;
@@ -569,27 +571,22 @@ __global__ __launch_bounds__(256, NE <= 5 ? 4 : (NE <= 8 ? 3 : 2)) void k_loglik
                 for (int i = 0; i < 4; ++i)
                     load(to[i], a.syn1, __builtin_amdgcn_readlane(my_pt, min(n0 + i, kWave - 1)), n0 + i < len);
             };
-            load_nodes(y, 0);
+            if (kAhead) load_nodes(y, 0);
             double h[NE];
 #pragma unroll
             for (int i = 0; i < NE; ++i) h[i] = 0.0;
-            for (int q = 0; q < P; q += 4) {
-                float x[4][NE];
+            for (int q = 0; q < P; ++q) {
+                const int pos = clo + q + (clo + q >= j ? 1 : 0);
+                float x[NE];
+                load(x, a.syn0, __builtin_amdgcn_readlane(r.sid, pos - r.j0 + kLLReach), true);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int pos = clo + q + k + (clo + q + k >= j ? 1 : 0);
-                    load(x[k], a.syn0, __builtin_amdgcn_readlane(r.sid, min(pos - r.j0 + kLLReach, kWave - 1)), q + k < P);
-                }
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-#pragma unroll
-                    for (int i = 0; i < NE; ++i) h[i] += static_cast<double>(x[k][i]);
+                for (int i = 0; i < NE; ++i) h[i] += static_cast<double>(x[i]);
             }
 #pragma unroll
             for (int i = 0; i < NE; ++i) h[i] = h[i] / static_cast<double>(P);
             double mine = 0.0;
             for (int n0 = 0; n0 < len; n0 += 4) {
-                load_nodes(yn, n0 + 4);
+                load_nodes(kAhead ? yn : y, kAhead ? n0 + 4 : n0);
                 double z[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
                 for (int i = 0; i < NE; ++i)
@@ -597,10 +594,12 @@ __global__ __launch_bounds__(256, NE <= 5 ? 4 : (NE <= 8 ? 3 : 2)) void k_loglik
                     for (int k = 0; k < 4; ++k) z[k] += h[i] * static_cast<double>(y[k][i]);
                 const double s = reduce4(z[0], z[1], z[2], z[3]);
                 mine = (lane & 15) == (n0 >> 2) ? s : mine;
+                if (kAhead) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
+                    for (int k = 0; k < 4; ++k)
 #pragma unroll
-                    for (int i = 0; i < NE; ++i) y[k][i] = yn[k][i];
+                        for (int i = 0; i < NE; ++i) y[k][i] = yn[k][i];
+                }
             }
             const int n = 4 * (lane & 15) + (lane >> 4);
             acc.add(((code >> n) & 1ull) ? -mine : mine, n < len);
