@@ -7,6 +7,7 @@
 #include <cstdint>
 
 #include "w2v_internal.h"
+#include "w2v_tiles.h"
 
 namespace w2v {
 
@@ -60,7 +61,7 @@ template <class F>
 __device__ __forceinline__ int32_t wave_partition_point(int32_t lo, int32_t hi, F pred) {
     const int lane = lane_id();
     while (lo < hi) {
-        const int32_t step = (hi - lo + kWave - 1) / kWave;
+        const int32_t step = probe_step(lo, hi);
         const int64_t at = lo + static_cast<int64_t>(lane + 1) * step - 1;
         const int n = __popcll(__ballot(at < hi && pred(static_cast<int32_t>(at))));
         const int64_t end = lo + static_cast<int64_t>(n + 1) * step - 1;   // the first failing probe, if there is one

@@ -1,7 +1,15 @@
 // Index arithmetic of the kernels' tiles that does not depend on the device, so that it can be checked on the host.
 #pragma once
 
+#include <stdint.h>
+
 namespace w2v {
+
+// Distance of the 64 probes of a search step over [lo, hi), lo < hi (any two values of that kind: the sum of their
+// distance and 63 may pass 2^31).
+constexpr int32_t probe_step(int32_t lo, int32_t hi) {
+    return static_cast<int32_t>((static_cast<uint32_t>(hi) - static_cast<uint32_t>(lo) + 63u) / 64u);
+}
 
 // The log-likelihood's tiles: rows of up to `columns` floats take `tiles` tiles of 64 columns, of which the first
 // `full` lie within every such row, and 4 `groups` window words a step; wider rows go in panels of that many tiles.

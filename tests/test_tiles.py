@@ -47,3 +47,22 @@ def test_loglik_reads_stay_in_the_row_and_cover_it(tmp_path, lo, hi):
             return 0;
         }}
     """)
+
+
+def test_search_steps_cover_ranges_of_any_length(tmp_path):
+    run_host(tmp_path, """
+        int main() {
+            for (int64_t n : {int64_t(1), int64_t(63), int64_t(64), int64_t(65), int64_t(1) << 20, (int64_t(1) << 31) - 65,
+                              (int64_t(1) << 31) - 64, (int64_t(1) << 31) - 1})
+                for (int64_t lo : {int64_t(0), int64_t(1), (int64_t(1) << 31) - 1 - n}) {
+                    if (lo < 0 || lo + n > (int64_t(1) << 31) - 1) continue;
+                    const int64_t step = probe_step(static_cast<int32_t>(lo), static_cast<int32_t>(lo + n));
+                    // 64 probes reach the range's end, and no fewer steps do
+                    if (step < 1 || 64 * step < n || 64 * (step - 1) >= n) {
+                        std::printf("lo %lld n %lld step %lld\\n", (long long)lo, (long long)n, (long long)step);
+                        return 1;
+                    }
+                }
+            return 0;
+        }
+    """)
