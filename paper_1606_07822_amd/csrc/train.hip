@@ -997,23 +997,30 @@ Variant pick_variant(int arch, int dim, bool buf, bool slide = false) {
 
 // Sixteen wavefronts a workgroup instead of twelve pay where the text (or the caller's number of workers) gives
 // nearly every compute unit such a workgroup. A shorter text has fewer wavefronts than fit (kMinUnitsPerWave work
-// units each): sixteen to a workgroup then crowd them onto fewer compute units. 2e6 tokens, V = 100K, 1e-3
-// subsampling, d = 200: 10.3 ms with twelve, 12.0 with sixteen (CBOW 6.5, 7.3). 4e6 tokens, 97 % of the compute
-// units: 13.2 with twelve, 12.4 with sixteen (8.4, 7.5).
+// units each): sixteen to a workgroup then crowd them onto fewer compute units. Calls at V = 100K, d = 200, 1e-3
+// subsampling: 2e6 tokens 10.3 ms with twelve, 12.0 with sixteen (CBOW 6.5, 7.3); 4e6 tokens, 97 % of the compute
+// units, 13.2 with twelve, 12.4 with sixteen (8.4, 7.5). The units that subsampling leaves empty count too (their
+// number is known on the device only): 4e6 to 1.2e7 tokens of 10K to 1M words take 0.86 to 1.03 of twelve's time at
+// 1e-4 to 1e-6, and up to 1.04 at 1e-7 (2 to 20 % of the tokens kept).
 bool fills_chip(int waves_per_block, int workers, int64_t n_units) {
     const int64_t waves = workers > 0 ? workers : n_units / kMinUnitsPerWave;
     return waves * 16 >= static_cast<int64_t>(waves_per_block) * device_cu_count() * 15;
 }
 
 // Word-row span at 129 to 256 columns: sixteen wavefronts a workgroup where the text fills the chip with them and
-// their centre records (and the stash, if asked for) fit beside the cache. What bounds these rows is the walk's chain of arithmetic and loads, which a fourth wavefront per SIMD
-// covers better than the registers it takes away cost (128 VGPRs, 16 spilled): 1e8 tokens' chunk of 2e7, V = 100K,
-// d = 200: skip-gram 49.3 -> 44.8 ms, CBOW 30.9 -> 27.4. At 300 columns CBOW spills too much (50 -> 90 ms), and
-// skip-gram without the span loses (50.4 -> 53.2).
+// their centre records (and the stash, if asked for) fit beside the cache. What bounds these rows is the walk's chain
+// of arithmetic and loads, which a fourth wavefront per SIMD covers better than the registers it takes away cost (128
+// VGPRs; skip-gram spills 12, CBOW off the store-only walk 5): 2e7 of 1e8 tokens, V = 100K, d = 200, 1e-4 subsampling: the skip-gram call 50.3 -> 46.0 ms, the CBOW call
+// 30.9 -> 27.4. At 300 columns CBOW spills too much (50 -> 90 ms), and skip-gram without the span loses (50.4 -> 53.2).
+template <int ARCH, int PF>
+constexpr Variant wide_span() {
+    constexpr int waves = 16, ne = 4, pg = 10;
+    return Variant{k_train<ne, pg, ARCH, waves, PF, true>, waves, ne, pg, lds_stride<ne>,
+                   waves * kSegLen * static_cast<int>(sizeof(int4))};
+}
 bool wide_span_variant(int arch, int dim, bool buf, bool stash, size_t cache_bytes, Variant *v) {
     if (dim <= 2 * kWave || dim > 4 * kWave) return false;
-    if (arch == 0) *v = variant<4, 10, 16, kPfBuf>(0, true);
-    else *v = buf ? variant<4, 10, 16, kPfBuf>(1, true) : variant<4, 10, 16, kPfAll>(1, true);
+    *v = arch == 0 ? wide_span<0, kPfBuf>() : buf ? wide_span<1, kPfBuf>() : wide_span<1, kPfAll>();
     const size_t stash_bytes = stash ? static_cast<size_t>(v->waves_per_block) * v->ne * kWave * sizeof(float) : 0;
     return cache_bytes + stash_bytes + static_cast<size_t>(v->rec_bytes) + 1024 <= device_max_lds();
 }
