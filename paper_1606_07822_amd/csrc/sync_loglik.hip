@@ -377,9 +377,11 @@ __device__ __forceinline__ uint64_t ll_code(const LLUnit &r, int c) {
 
 // Sum of log sigmoids as one logarithm: log sigmoid(u) = min(u, 0) - log(1 + exp(-|u|)), and the logarithms of
 // many factors in (1, 2] are the logarithm of their product (a lane takes at most 5 groups x 4 blocks of nodes x
-// kLLSeg centres = 160 factors, so the product stays below 2^160). Each factor adds 2^-53 to the sum's absolute
-// error, as its own logarithm would; below 2^-10, where that would show beside the term itself, the term is
-// summed directly, by five terms of its series (relative error below 2^-52).
+// kLLSeg centres = 160 factors, so the product stays below 2^160). A factor's sum and its product each round, so a
+// factor adds up to 2^-52 to the sum's absolute error (beside the exponential's own). Below 2^-10, where that would
+// show beside the term itself, the term is summed directly, by five terms of its series (the terms left out are below
+// 2^-52 of it). Measured against log1p in 80 bits (2e7 terms, 4e5 lanes of 160 factors): the series is off by up to
+// 2.6e-16 of the term, the factors by up to 6.6e-15 in all and by 1.8e-15 of their sum.
 struct LogSigmoidSum {
     double sum = 0.0, product = 1.0;
     __device__ __forceinline__ void add(double u, bool live) {

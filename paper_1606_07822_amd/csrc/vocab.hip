@@ -526,9 +526,17 @@ int run_build_vocab(const int32_t *tokens, int64_t n_tokens, int32_t id_space, i
     k_zero_counts<<<static_cast<unsigned>(ceil_div(id_space, 256)), 256, 0, s>>>(counts, id_space, scal);
     W2V_LAUNCH_CHECK("zero");
     const int32_t width = static_cast<int32_t>(ceil_div(id_space, kBuckets));
-    // lists pay where memory's atomics would take most of the time: texts of some millions of tokens, with ids past
-    // the bins, whose ranges fit LDS and whose remapped text has room for them; places in the lists' partition (at
-    // most half as many as tokens) are 32 bits
+    // Lists pay where memory's atomics would take most of the time: texts of some millions of tokens, with ids past
+    // the bins, whose ranges fit LDS and whose remapped text has room for them (without one the atomics stay); places
+    // in the lists' partition (at most half as many as tokens) are 32 bits. Whole call with and without them, us:
+    //                          1e6 tokens   4e6          8e6          1.6e7        3.2e7
+    //   200K ids, Zipf ranks   151 / 132    181 / 174    208 / 222    258 / 295    334 / 434
+    //   1M ids, Zipf ranks     160 / 158    193 / 208    230 / 275    297 / 392    413 / 623
+    //   50K ids, scattered     239 / 1183   236 / 522    823 / 8593   1454 / 17066 2683 / 33998
+    //   50K ids, Zipf ranks    156 / 130    183 / 149    212 / 189    258 / 230    318 / 298
+    //   36,865 ids, Zipf ranks 154 / 129    174 / 156    193 / 184    232 / 214    280 / 265
+    // (scattered: the frequent ids lie anywhere). The lists cost some 20 us of launches where next to no id is past
+    // the bins, which the ids' number does not tell; without them frequent ids there cost milliseconds.
     if (tokens_out && n_tokens >= kListTokens && n_tokens <= kListTokensMost && id_space > kHotBins &&
         width <= kHotBins) {
         const int64_t cap = std::min<int64_t>(n_tokens / 2 / kListGroups, INT32_MAX);
