@@ -205,9 +205,9 @@ __global__ __launch_bounds__(kMergeThreads) void k_huff_merge(const int64_t *__r
     }
 }
 
-// codelen / code per leaf; error flag (code longer than 64, or a node that was never merged). Depth does not fall along the queues (the inner
-// queue is first in, first out, so an earlier node's parent is never later), so the last word has the longest
-// code.
+// codelen / code per leaf; error flag (code longer than 64, or a node that was never merged). Depth does not fall
+// along the queues (the inner queue is first in, first out, so an earlier node's parent is never later), so the last
+// word has the longest code.
 __global__ void k_huff_codes(const uint32_t *__restrict__ up, int32_t V, uint8_t *__restrict__ codelen,
                              uint64_t *__restrict__ code, int32_t *__restrict__ flags) {
     const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;

@@ -1010,8 +1010,9 @@ bool fills_chip(int waves_per_block, int workers, int64_t n_units) {
 // Word-row span at 129 to 256 columns: sixteen wavefronts a workgroup where the text fills the chip with them and
 // their centre records (and the stash, if asked for) fit beside the cache. What bounds these rows is the walk's chain
 // of arithmetic and loads, which a fourth wavefront per SIMD covers better than the registers it takes away cost (128
-// VGPRs; skip-gram spills 12, CBOW off the store-only walk 5): 2e7 of 1e8 tokens, V = 100K, d = 200, 1e-4 subsampling: the skip-gram call 50.3 -> 46.0 ms, the CBOW call
-// 30.9 -> 27.4. At 300 columns CBOW spills too much (50 -> 90 ms), and skip-gram without the span loses (50.4 -> 53.2).
+// VGPRs; skip-gram spills 12, CBOW off the store-only walk 5): 2e7 of 1e8 tokens, V = 100K, d = 200, 1e-4 subsampling,
+// the skip-gram call 50.2 -> 46.0 ms, the CBOW call 30.9 -> 27.4. At 300 columns CBOW spills too much (50 -> 90 ms),
+// and skip-gram without the span loses (50.4 -> 53.2).
 template <int ARCH, int PF>
 constexpr Variant wide_span() {
     constexpr int waves = 16, ne = 4, pg = 10;
