@@ -24,7 +24,7 @@ int train_launch_shape(int arch, int dim, int cache_k, bool delta, bool buf, int
                        int *waves);
 int64_t train_egrad_floats(int arch, int dim, bool buf, int stride, int window, int waves);
 int train_word_span(int arch, int dim, bool buf, int write_policy, int window);
-int launch_train_async(TrainArgs a, int arch, int window, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s,
+int launch_train_async(TrainArgs a, int arch, int window, double raw_tokens, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s,
                        int64_t *stats_out, const int64_t *totals);
 size_t sync_extra_bytes(int32_t V, int32_t dim, int64_t n_docs);
 int run_train_sync(const w2v_model *m, const w2v_params *p, const SampleBufs &b, int64_t n_tokens, Carve &c,
@@ -389,7 +389,8 @@ int w2v_train_hs_epoch(const w2v_model *m, const int32_t *tokens, int64_t n_toke
     a.egrad = n_egrad > 0 ? egrad : nullptr;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (int rc = timing_events(&ev0, &ev1)) return rc;
-    return launch_train_async(a, p->arch, p->window, ev0, ev1, s, stats, b.totals);
+    const double raw_tokens = static_cast<double>(p->n_epochs) * static_cast<double>(p->corpus_tokens);
+    return launch_train_async(a, p->arch, p->window, raw_tokens, ev0, ev1, s, stats, b.totals);
 }
 
 int32_t w2v_train_word_span(const w2v_model *m, const w2v_params *p) {

@@ -1007,8 +1007,15 @@ bool fills_chip(int waves_per_block, int workers, int64_t n_units) {
     return waves * 16 >= static_cast<int64_t>(waves_per_block) * device_cu_count() * 15;
 }
 
-// Word-row span at 129 to 256 columns: sixteen wavefronts a workgroup where the text fills the chip with them and
-// their centre records (and the stash, if asked for) fit beside the cache. What bounds these rows is the walk's chain
+// The span's rows are stored, so more wavefronts at once overwrite more of each other's changes. What a model keeps
+// of its gain over the untrained one with sixteen wavefronts, of that with twelve (3,072 and 4,096 at once; from zero
+// output rows, d = 200, V = 5K to 1M, 1e-3 to 1e-5 subsampling): 0.14 to 0.39 after 4e6 tokens, 0.21 to 1.00 after
+// 8e6, 0.87 to 1.00 after 1.6e7, 0.92 to 1.00 after 3.2e7 and 6.4e7, skip-gram 0.99 to 1.00 after 1e8 (CBOW 0.96 to
+// 1.00), CBOW 0.99 to 1.00 after 2e8, whether in one call or in chunks of 8e6. So the whole training decides.
+bool long_training(int arch, double raw_tokens) { return raw_tokens >= (arch == 0 ? 1e8 : 2e8); }
+
+// Word-row span at 129 to 256 columns: sixteen wavefronts a workgroup where the text fills the chip with them, the
+// training is long and their centre records (and the stash, if asked for) fit beside the cache. What bounds these rows is the walk's chain
 // of arithmetic and loads, which a fourth wavefront per SIMD covers better than the registers it takes away cost (128
 // VGPRs; skip-gram spills 12, CBOW off the store-only walk 5): 2e7 of 1e8 tokens, V = 100K, d = 200, 1e-4 subsampling,
 // the skip-gram call 50.2 -> 46.0 ms, the CBOW call 30.9 -> 27.4. At 300 columns CBOW spills too much (50 -> 90 ms),
@@ -1106,12 +1113,12 @@ int train_word_span(int arch, int dim, bool buf, int write_policy, int window) {
     return train_slide(arch, dim, buf, write_policy, window) ? pick_variant(arch, dim, buf, true).pg / 2 : 0;
 }
 
-int launch_train_async(TrainArgs a, int arch, int window, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s,
+int launch_train_async(TrainArgs a, int arch, int window, double raw_tokens, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s,
                        int64_t *stats_out, const int64_t *totals) {
     const bool slide = train_slide(arch, a.dim, a.stores_only != 0, a.write_policy, window);
     Variant v;
     const size_t wide_cache = (a.cache_delta ? 1ull : 2ull) * a.cache_k * lds_stride<4>(a.dim) * sizeof(float);
-    if (!(slide && fills_chip(16, a.workers, a.n_units) &&
+    if (!(slide && long_training(arch, raw_tokens) && fills_chip(16, a.workers, a.n_units) &&
           wide_span_variant(arch, a.dim, a.stores_only != 0, a.span_stash != 0, wide_cache, &v)))
         v = pick_variant(arch, a.dim, a.stores_only != 0, slide);
     const size_t cache_lds = (a.cache_delta ? 1ull : 2ull) * a.cache_k * v.ls(a.dim) * sizeof(float);
